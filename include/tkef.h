@@ -309,8 +309,8 @@ int tkef_update_plan_set_value_format(tkef_update_plan plan, int32_t format);
  * that sequential sum. on = 0 (default): the entries of a position are
  * added in whatever order the device runs them (results within the
  * documented tolerance of the sequential sum, exact with two or fewer
- * entries per position). The ordered sum costs LDS and time (a counting
- * sort of each chunk of entries per update tile). Host only;
+ * entries per position). The ordered sum costs LDS and time (the
+ * entries that share a position are put in order per update tile). Host only;
  * TKEF_EINVAL for other values. */
 int tkef_update_plan_set_deterministic(tkef_update_plan plan, int32_t on);
 

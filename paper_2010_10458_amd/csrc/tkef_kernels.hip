@@ -1772,7 +1772,6 @@ constexpr int kXcdRun = 16;                   // consecutive update tiles one di
 constexpr int kUVecPerThread = kUTile / 4 / kUBlock;  // float4 per thread per tile
 
 constexpr int kPairUnroll = 4;  // list entries per thread and chunk of the accumulation
-constexpr int kUOwn = kUTile / kUBlock;  // tile positions one thread owns in the ordered sum
 
 // The ordered accumulation of one chunk of list entries (deterministic mode).
 // Entry j * kUBlock + tid of the chunk (li[j], vv[j]; li outside [0, len)
@@ -1780,27 +1779,35 @@ constexpr int kUOwn = kUTile / kUBlock;  // tile positions one thread owns in th
 // are numbered in worker order, then list order, as Alg. 2 visits them.
 // Each position's entries are added to acc in that order, one binary32 add
 // at a time, so the sums do not depend on the order in which threads run:
-//   1. LDS counters count every position's entries (word w holds the 16-bit
-//      counts of positions w and w + kUTile / 2); each entry keeps its
-//      arrival rank at its position;
-//   2. thread t owns the words t, t + kUBlock, ... (so a wavefront's LDS
-//      accesses fall in distinct banks) and with them kUOwn positions: an
-//      exclusive scan of the counts gives every position a first slot (the
-//      positions' slot ranges are disjoint; their order does not matter);
-//   3. each entry goes to slot first + rank of (dq: entry number, dv: value);
-//   4. each owner sorts its positions' slots by entry number (insertion
-//      sort; a position usually has one entry) and adds them in that order.
-// dcnt: kUTile / 2 words, zero on entry and on return; dq, dv: kUBlock *
-// kPairUnroll slots; dws: kUBlock / 64 words. Uniform in the workgroup.
+//   1. every entry counts itself at its position (16-bit counters, positions
+//      w and w + kUTile / 2 share word w) and keeps its arrival rank;
+//   2. the first to arrive at a position reads the count: an entry alone at
+//      its position is added at once; otherwise the first arrival takes a run
+//      of count + 1 slots, whose head holds the count, and leaves the run's
+//      number in the position's counter;
+//   3. every entry of such a position puts its number into the run (dq), in
+//      arrival order;
+//   4. each reads the run's numbers: the smaller ones among them are its rank
+//      in worker order, where it puts its value (dv);
+//   5. the first arrival adds the values in that order and zeroes the counter.
+// Every step takes one entry per thread and chunk, so its LDS latencies
+// overlap; the only serial chain is the sum of a position's values. (Before,
+// each thread sorted and added the entries of its sixteen positions one after
+// another. k_update, momentum, P = 128 lists of 25,600 entries, 25.6 M
+// parameters: 99 us then and 85 now with positions drawn uniformly, 276 and
+// 89 us when a quarter of the entries lie at positions that about sixteen
+// workers name, 661 and 95 us when half do at about 32; any order: 77 us.)
+// dcnt: kUTile / 2 words, zero on entry and on return; dq, dv: kDetSlots
+// slots; dtop: one word, zero on entry and on return. Uniform in the
+// workgroup; ends with a barrier.
+constexpr int kDetSlots = kUBlock * kPairUnroll * 3 / 2;  // runs hold two entries or more
 __device__ __forceinline__ void det_accumulate(const int32_t (&li)[kPairUnroll],
                                                const float (&vv)[kPairUnroll], int32_t len,
                                                bool sparse_mode, float* acc, uint32_t* mask,
                                                uint32_t* dcnt, uint16_t* dq, float* dv,
-                                               uint32_t* dws) {
-  static_assert(kUBlock * kPairUnroll <= 65535, "slots and entry numbers fit 16 bits");
-  static_assert(kUOwn % 2 == 0, "two counts per word");
+                                               uint32_t* dtop) {
+  static_assert(kDetSlots <= 65535, "slots and entry numbers fit 16 bits");
   constexpr int kHalf = kUTile / 2;  // position p: word p % kHalf, half p / kHalf
-  constexpr int kWords = kUOwn / 2;  // words per thread
   const int tid = threadIdx.x;
   uint32_t rank[kPairUnroll];
 #pragma unroll
@@ -1812,62 +1819,65 @@ __device__ __forceinline__ void det_accumulate(const int32_t (&li)[kPairUnroll],
     }
   }
   __syncthreads();
-  uint32_t cw[kWords];  // this thread's counts, two per word
-  uint32_t mine = 0u;
+  // run[j]: the run of this entry's position (none: the entry is done)
+  uint32_t run[kPairUnroll], cnt[kPairUnroll];
 #pragma unroll
-  for (int i = 0; i < kWords; ++i) {
-    cw[i] = dcnt[tid + i * kUBlock];
-    mine += (cw[i] & 0xFFFFu) + (cw[i] >> 16);
+  for (int j = 0; j < kPairUnroll; ++j) {
+    run[j] = cnt[j] = 0u;
+    const bool in = li[j] >= 0 && li[j] < len;
+    if (in && rank[j] == 0u) {
+      // (only first arrivals read or change the counters in this step)
+      const uint32_t sh = li[j] >= kHalf ? 16u : 0u;
+      uint32_t* word = &dcnt[li[j] & (kHalf - 1)];
+      const uint32_t c = (*word >> sh) & 0xFFFFu;
+      if (sparse_mode) atomicOr(&mask[li[j] >> 5], 1u << (li[j] & 31));
+      if (c == 1u) {
+        acc[li[j]] = acc[li[j]] + vv[j];
+        atomicXor(word, 1u << sh);
+      } else {
+        cnt[j] = c;
+        run[j] = atomicAdd(dtop, c + 1u);
+        dq[run[j]] = (uint16_t)c;
+        atomicXor(word, (c ^ run[j]) << sh);
+      }
+    }
   }
-  uint32_t total;
-  const uint32_t first = block_scan<kUBlock>(mine, dws, &total);  // (ends with a barrier)
-  uint32_t o = first;
+  __syncthreads();
+  if (*dtop == 0u) return;  // (uniform) every entry was alone
 #pragma unroll
-  for (int i = 0; i < kWords; ++i) {
-    const uint32_t c0 = cw[i] & 0xFFFFu, c1 = cw[i] >> 16;
-    dcnt[tid + i * kUBlock] = o | ((o + c0) << 16);  // first slots
-    o += c0 + c1;
+  for (int j = 0; j < kPairUnroll; ++j) {
+    const bool in = li[j] >= 0 && li[j] < len;
+    if (in && rank[j] != 0u) {
+      const uint32_t sh = li[j] >= kHalf ? 16u : 0u;
+      run[j] = (dcnt[li[j] & (kHalf - 1)] >> sh) & 0xFFFFu;
+      cnt[j] = dq[run[j]];
+    }
+    if (cnt[j]) dq[run[j] + 1u + rank[j]] = (uint16_t)(j * kUBlock + tid);
+  }
+  __syncthreads();
+  if (tid == 0) *dtop = 0u;
+#pragma unroll
+  for (int j = 0; j < kPairUnroll; ++j) {
+    if (cnt[j]) {
+      const uint32_t me = (uint32_t)(j * kUBlock + tid), r0 = run[j] + 1u;
+      uint32_t before = 0u;
+#pragma unroll 4
+      for (uint32_t i = 0; i < cnt[j]; ++i) before += dq[r0 + i] < me ? 1u : 0u;
+      dv[r0 + before] = vv[j];
+    }
   }
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < kPairUnroll; ++j) {
-    if (li[j] >= 0 && li[j] < len) {
+    if (cnt[j] && rank[j] == 0u) {
       const uint32_t sh = li[j] >= kHalf ? 16u : 0u;
-      const uint32_t slot = ((dcnt[li[j] & (kHalf - 1)] >> sh) & 0xFFFFu) + rank[j];
-      dq[slot] = (uint16_t)(j * kUBlock + tid);
-      dv[slot] = vv[j];
+      float sum = acc[li[j]];
+#pragma unroll 4
+      for (uint32_t i = 0; i < cnt[j]; ++i) sum = sum + dv[run[j] + 1u + i];
+      acc[li[j]] = sum;
+      atomicXor(&dcnt[li[j] & (kHalf - 1)], run[j] << sh);
     }
   }
-  __syncthreads();
-  o = first;
-#pragma unroll 1
-  for (int i = 0; i < kUOwn; ++i) {
-    const uint32_t c = (i & 1) ? (cw[i >> 1] >> 16) : (cw[i >> 1] & 0xFFFFu);
-    if (c == 0u) continue;
-    const uint32_t e = o + c;
-#pragma unroll 1
-    for (uint32_t a = o + 1; a < e; ++a) {
-      const uint16_t kq = dq[a];
-      const float kv = dv[a];
-      uint32_t b = a;
-      while (b > o && dq[b - 1] > kq) {
-        dq[b] = dq[b - 1];
-        dv[b] = dv[b - 1];
-        --b;
-      }
-      dq[b] = kq;
-      dv[b] = kv;
-    }
-    const int pos = tid + (i >> 1) * kUBlock + (i & 1) * kHalf;
-    float sum = acc[pos];
-#pragma unroll 1
-    for (uint32_t a = o; a < e; ++a) sum = sum + dv[a];
-    acc[pos] = sum;
-    if (sparse_mode) atomicOr(&mask[pos >> 5], 1u << (pos & 31));
-    o = e;
-  }
-#pragma unroll
-  for (int i = 0; i < kWords; ++i) dcnt[tid + i * kUBlock] = 0u;
   __syncthreads();
 }
 
@@ -1899,11 +1909,11 @@ __global__ __launch_bounds__(kUBlock) void k_update(
   // per-worker form: the list pointers of the current batch of workers
   __shared__ const int32_t* s_ip[kTable ? kUBlock : 1];
   __shared__ const float* s_vp[kTable ? kUBlock : 1];
-  // deterministic mode: counters, slots and scan words of det_accumulate
+  // deterministic mode: counters and slots of det_accumulate
   __shared__ uint32_t dcnt[kDet ? kUTile / 2 : 1];
-  __shared__ uint16_t dq[kDet ? kUBlock * kPairUnroll : 1];
-  __shared__ float dv[kDet ? kUBlock * kPairUnroll : 1];
-  __shared__ uint32_t dws[kDet ? kUBlock / 64 : 1];
+  __shared__ uint16_t dq[kDet ? kDetSlots : 1];
+  __shared__ float dv[kDet ? kDetSlots : 1];
+  __shared__ uint32_t dtop;
   const int tid = threadIdx.x;
   // Workgroups go round-robin to the XCDs; give each XCD runs of kXcdRun
   // consecutive tiles, so that neighbouring tiles, which share the cache
@@ -1945,8 +1955,10 @@ __global__ __launch_bounds__(kUBlock) void k_update(
   for (int i = tid; i < kUTile; i += kUBlock) acc[i] = 0.0f;
   if (sparse_mode)
     for (int i = tid; i < kUTile / 32; i += kUBlock) mask[i] = 0u;
-  if constexpr (kDet)
+  if constexpr (kDet) {
     for (int i = tid; i < kUTile / 2; i += kUBlock) dcnt[i] = 0u;
+    if (tid == 0) dtop = 0u;
+  }
   __syncthreads();
 
   // 1. accumulate every worker's entries that fall in this tile
@@ -2006,7 +2018,7 @@ __global__ __launch_bounds__(kUBlock) void k_update(
         }
       }
       if constexpr (kDet) {
-        det_accumulate(li, vv, len, sparse_mode, acc, mask, dcnt, dq, dv, dws);
+        det_accumulate(li, vv, len, sparse_mode, acc, mask, dcnt, dq, dv, &dtop);
       } else {
 #pragma unroll
         for (int j = 0; j < kPairUnroll; ++j) {
