@@ -199,10 +199,6 @@ __device__ __forceinline__ void put_val(void* out, size_t pos, float x, int val1
   if (val16) reinterpret_cast<uint16_t*>(out)[pos] = __half_as_ushort(__float2half_rn(x));
   else reinterpret_cast<float*>(out)[pos] = x;
 }
-__device__ __forceinline__ float get_val(const void* in, size_t pos, int val16) {
-  return val16 ? __half2float(__ushort_as_half(reinterpret_cast<const uint16_t*>(in)[pos]))
-               : reinterpret_cast<const float*>(in)[pos];
-}
 
 }  // namespace
 
@@ -1771,7 +1767,106 @@ constexpr int kXcds = 8;                      // MI355X: 8 accelerator dies
 constexpr int kXcdRun = 16;                   // consecutive update tiles one die takes
 constexpr int kUVecPerThread = kUTile / 4 / kUBlock;  // float4 per thread per tile
 
-constexpr int kPairUnroll = 4;  // list entries per thread and chunk of the accumulation
+constexpr int kPairUnroll = 3;  // list entries per thread and chunk of the accumulation
+
+// The workers of a thread's entries e[] of a tile: the first w with scan[w] >
+// e, scan the inclusive prefix of the workers' counts in the tile (kUBlock
+// words, the last above every e). A fixed number of steps, the searches side
+// by side, so that their LDS reads overlap.
+__device__ __forceinline__ void entry_workers(const uint32_t* scan,
+                                              const uint32_t (&e)[kPairUnroll],
+                                              int (&w)[kPairUnroll]) {
+#pragma unroll
+  for (int j = 0; j < kPairUnroll; ++j) w[j] = 0;
+#pragma unroll
+  for (int step = kUBlock / 2; step >= 1; step >>= 1) {
+    uint32_t s[kPairUnroll];
+#pragma unroll
+    for (int j = 0; j < kPairUnroll; ++j) s[j] = scan[w[j] + step - 1];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < kPairUnroll; ++j) w[j] += s[j] <= e[j] ? step : 0;
+  }
+}
+
+// Where a list entry lies: the gathered layout's arrays and an entry number,
+// or (kTable) the worker's own arrays.
+template <bool kTable>
+struct PairSrc {
+  const int32_t* idx;
+  const void* val;
+  int64_t stride;
+  const int32_t* const* ip;  // kTable: the batch's list pointers (LDS)
+  const float* const* vp;
+  struct Ref {
+    const int32_t* i;
+    const float* v;
+    int64_t n;
+  };
+  __device__ __forceinline__ Ref at(int p0, int w, int64_t jj) const {
+    if constexpr (kTable) return Ref{ip[w] + jj, vp[w] + jj, 0};
+    else return Ref{nullptr, nullptr, (int64_t)(p0 + w) * stride + jj};
+  }
+  __device__ __forceinline__ int32_t pos(const Ref& r) const {
+    if constexpr (kTable) return *(const gint*)r.i;
+    else return idx[r.n];
+  }
+  __device__ __forceinline__ uint16_t half(const Ref& r) const {
+    if constexpr (kTable) return 0;  // (that form holds binary32 values)
+    else return reinterpret_cast<const uint16_t*>(val)[r.n];
+  }
+  __device__ __forceinline__ float full(const Ref& r) const {
+    if constexpr (kTable) return *gptr(r.v);
+    else return reinterpret_cast<const float*>(val)[r.n];
+  }
+};
+
+// This thread's entries q0 + j * kUBlock + tid of a tile's `total` (> 0; li:
+// position relative to the tile, -1 for none; sbeg: the workers' first entries
+// in the tile). All loads are in flight together: entries past the end read
+// the last one, and the value format is decided once for all of them: decided
+// at each value, it put a wait for every value between the loads. With that
+// wait, four entries per thread and a branching search one after another:
+// P = 128 lists of 25,600 entries, 25.6 M parameters, k_update 76.0 us
+// (momentum), 89 (momentum, ordered, a quarter of the entries at shared
+// positions), 49.2 (LARS norms); now 72.8, 80, 45.0; four entries per thread:
+// 73.2 and 46.6 (momentum, norms), two: 73.8 and 46.5. (Two threads
+// walking each worker's own segment, without search or scan: 77.2; several
+// tiles per workgroup with the next tile's entries prefetched: 79-95.)
+template <bool kTable>
+__device__ __forceinline__ void load_pairs(const PairSrc<kTable>& src, const uint32_t* scan,
+                                           const int32_t* sbeg, int p0, uint32_t q0,
+                                           uint32_t total, int32_t base, int val16,
+                                           int32_t (&li)[kPairUnroll],
+                                           float (&vv)[kPairUnroll]) {
+  uint32_t e[kPairUnroll];
+  int w[kPairUnroll];
+#pragma unroll
+  for (int j = 0; j < kPairUnroll; ++j)
+    e[j] = min(q0 + j * kUBlock + threadIdx.x, total - 1u);
+  entry_workers(scan, e, w);
+  typename PairSrc<kTable>::Ref ref[kPairUnroll];
+#pragma unroll
+  for (int j = 0; j < kPairUnroll; ++j) {
+    const uint32_t before = scan[max(w[j] - 1, 0)];
+    ref[j] = src.at(p0, w[j], (int64_t)sbeg[w[j]] + (e[j] - (w[j] ? before : 0u)));
+  }
+#pragma unroll
+  for (int j = 0; j < kPairUnroll; ++j) li[j] = src.pos(ref[j]);
+  if (val16) {
+    uint16_t hv[kPairUnroll];
+#pragma unroll
+    for (int j = 0; j < kPairUnroll; ++j) hv[j] = src.half(ref[j]);
+#pragma unroll
+    for (int j = 0; j < kPairUnroll; ++j) vv[j] = __half2float(__ushort_as_half(hv[j]));
+  } else {
+#pragma unroll
+    for (int j = 0; j < kPairUnroll; ++j) vv[j] = src.full(ref[j]);
+  }
+#pragma unroll
+  for (int j = 0; j < kPairUnroll; ++j)
+    li[j] = q0 + j * kUBlock + threadIdx.x < total ? li[j] - base : -1;
+}
 
 // The ordered accumulation of one chunk of list entries (deterministic mode).
 // Entry j * kUBlock + tid of the chunk (li[j], vv[j]; li outside [0, len)
@@ -1794,9 +1889,10 @@ constexpr int kPairUnroll = 4;  // list entries per thread and chunk of the accu
 // overlap; the only serial chain is the sum of a position's values. (Before,
 // each thread sorted and added the entries of its sixteen positions one after
 // another. k_update, momentum, P = 128 lists of 25,600 entries, 25.6 M
-// parameters: 99 us then and 85 now with positions drawn uniformly, 276 and
-// 89 us when a quarter of the entries lie at positions that about sixteen
-// workers name, 661 and 95 us when half do at about 32; any order: 77 us.)
+// parameters, both with load_pairs as it was: 99 us then and 85 now with
+// positions drawn uniformly, 276 and 89 us when a quarter of the entries lie
+// at positions that about sixteen workers name, 661 and 95 us when half do at
+// about 32.)
 // dcnt: kUTile / 2 words, zero on entry and on return; dq, dv: kDetSlots
 // slots; dtop: one word, zero on entry and on return. Uniform in the
 // workgroup; ends with a barrier.
@@ -1881,6 +1977,149 @@ __device__ __forceinline__ void det_accumulate(const int32_t (&li)[kPairUnroll],
   __syncthreads();
 }
 
+// One update tile: number, first position, positions, first tensor; where its
+// w (and b) lie if it is inside one tensor and they start 16-byte aligned
+// (fast).
+struct UpdTile {
+  int32_t u, base, len, t0;
+  float* w;
+  float* b;
+  bool fast;
+};
+
+// LARS norms: per tensor of the tile, the sums of w^2 and G^2 (double) into
+// its pair. wv: the tile's w (fast tiles). Uniform in the workgroup; ends with
+// a barrier.
+__device__ __forceinline__ void tile_norms(const UpdTensor* __restrict__ tens,
+                                           const int32_t* __restrict__ tile_first, int32_t ntens,
+                                           const UpdTile& ut, const float4 (&wv)[kUVecPerThread],
+                                           const float* acc, const LarsArgs& lars, double* lred) {
+  const int tid = threadIdx.x;
+  const int32_t tl = ut.fast ? ut.t0 : min(tile_first[ut.u + 1], ntens - 1);
+  for (int ti = ut.t0; ti <= tl; ++ti) {
+    const UpdTensor tt = tens[ti];
+    const int64_t a = max((int64_t)ut.base, tt.goff);
+    const int64_t z = min((int64_t)ut.base + ut.len, tt.goff + tt.n);
+    if (z <= a) continue;  // (uniform in the workgroup)
+    double sw = 0.0, sg = 0.0;
+    if (ut.fast) {
+      const float4* a4 = reinterpret_cast<const float4*>(acc);
+#pragma unroll
+      for (int q = 0; q < kUVecPerThread; ++q) {
+        const float4 G = a4[q * kUBlock + tid];
+        const float4 w = wv[q];
+        sw += (double)w.x * w.x + (double)w.y * w.y + (double)w.z * w.z + (double)w.w * w.w;
+        sg += (double)G.x * G.x + (double)G.y * G.y + (double)G.z * G.z + (double)G.w * G.w;
+      }
+    } else {
+      const gfloat* w = gptr(tt.w + (a - tt.goff));
+      const int la = (int)(a - ut.base), cnt = (int)(z - a);
+      for (int q = tid; q < cnt; q += kUBlock) {
+        const double wq = w[q], gq = acc[la + q];
+        sw += wq * wq;
+        sg += gq * gq;
+      }
+    }
+    const double2 r = ublock_sum2(sw, sg, lred);
+    if (tid == 0) lars.part[lars.tpair[ti] + (ut.u - (int32_t)(tt.goff >> kUShift))] = r;
+  }
+}
+
+// The step (or, densify, the dense sums) of a fast tile from its prefetched w
+// and b.
+__device__ __forceinline__ void tile_step_fast(const UpdTile& ut,
+                                               const float4 (&wv)[kUVecPerThread],
+                                               const float4 (&bv)[kUVecPerThread], const float* acc,
+                                               bool densify, bool lapply, bool mom, float rate,
+                                               float lr, float mu, float wd, float eps) {
+  const int tid = threadIdx.x;
+  float4* w4 = reinterpret_cast<float4*>(ut.w);
+  float4* b4 = reinterpret_cast<float4*>(ut.b);
+  const float4* a4 = reinterpret_cast<const float4*>(acc);
+#pragma unroll
+  for (int q = 0; q < kUVecPerThread; ++q) {
+    const int v = q * kUBlock + tid;
+    const float4 G = a4[v];
+    if (densify) {
+      store_nt4(w4 + v, G);
+      continue;
+    }
+    float4 w = wv[q], bb = mom ? bv[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+    if (lapply) {
+      w.x = lars_step(G.x, w.x, bb.x, mom, rate, mu, eps);
+      w.y = lars_step(G.y, w.y, bb.y, mom, rate, mu, eps);
+      w.z = lars_step(G.z, w.z, bb.z, mom, rate, mu, eps);
+      w.w = lars_step(G.w, w.w, bb.w, mom, rate, mu, eps);
+    } else {
+      w.x = sgd_step(G.x, w.x, bb.x, mom, lr, mu, wd);
+      w.y = sgd_step(G.y, w.y, bb.y, mom, lr, mu, wd);
+      w.z = sgd_step(G.z, w.z, bb.z, mom, lr, mu, wd);
+      w.w = sgd_step(G.w, w.w, bb.w, mom, lr, mu, wd);
+    }
+    store_nt4(w4 + v, w);
+    if (mom) store_nt4(b4 + v, bb);
+  }
+}
+
+// The same for any other tile, tensor by tensor.
+__device__ __forceinline__ void tile_step_general(const UpdTensor* __restrict__ tens,
+                                                  int32_t ntens, const UpdTile& ut,
+                                                  const float* acc, bool densify, bool lapply,
+                                                  bool mom, float lr, float mu, float wd,
+                                                  const LarsArgs& lars) {
+  const int tid = threadIdx.x;
+  const int32_t base = ut.base, len = ut.len;
+  for (int ti = ut.t0; ti < ntens; ++ti) {
+    const UpdTensor tt = tens[ti];
+    if (tt.goff >= (int64_t)base + len) break;
+    const int64_t a = max((int64_t)base, tt.goff);
+    const int64_t z = min((int64_t)base + len, tt.goff + tt.n);
+    if (z <= a) continue;
+    const int cnt = (int)(z - a);
+    const int la = (int)(a - base);
+    gfloat* __restrict__ w = gptr(tt.w + (a - tt.goff));
+    gfloat* __restrict__ bm = mom ? gptr(tt.b + (a - tt.goff)) : nullptr;
+    const bool vec = ((reinterpret_cast<uintptr_t>(w) |
+                       (bm ? reinterpret_cast<uintptr_t>(bm) : 0u)) & 15u) == 0;
+    const float rate = lapply ? (float)lars.rate[ti] : 0.0f;
+    auto step = [&](float G, float wq, float& bq) -> float {
+      return lapply ? lars_step(G, wq, bq, mom, rate, mu, lars.eps)
+                    : sgd_step(G, wq, bq, mom, lr, mu, wd);
+    };
+    int done = 0;
+    if (vec) {
+      const int nv = cnt >> 2;
+      gv4f* w4 = (gv4f*)w;
+      gv4f* b4 = (gv4f*)bm;
+      for (int q = tid; q < nv; q += kUBlock) {
+        if (densify) {
+          const int l = la + 4 * q;
+          w4[q] = v4f{acc[l], acc[l + 1], acc[l + 2], acc[l + 3]};
+          continue;
+        }
+        const v4f wv4 = w4[q];
+        const v4f bv4 = bm ? b4[q] : v4f{0.f, 0.f, 0.f, 0.f};
+        float wq[4] = {wv4.x, wv4.y, wv4.z, wv4.w}, bq[4] = {bv4.x, bv4.y, bv4.z, bv4.w};
+        const int l = la + 4 * q;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) wq[c] = step(acc[l + c], wq[c], bq[c]);
+        w4[q] = v4f{wq[0], wq[1], wq[2], wq[3]};
+        if (mom) b4[q] = v4f{bq[0], bq[1], bq[2], bq[3]};
+      }
+      done = nv << 2;
+    }
+    for (int q = done + tid; q < cnt; q += kUBlock) {
+      if (densify) {
+        w[q] = acc[la + q];
+        continue;
+      }
+      float bq = mom ? bm[q] : 0.0f;
+      w[q] = step(acc[la + q], w[q], bq);
+      if (mom) bm[q] = bq;
+    }
+  }
+}
+
 // kLars: the LARS norm and step passes (a separate instantiation, so the SGD
 // and aggregation passes keep their register budget).
 // kTable: the lists come as a table of per-worker pointers (binary32 values).
@@ -1893,8 +2132,6 @@ __global__ __launch_bounds__(kUBlock) void k_update(
     const int32_t* __restrict__ seg, float lr, float mu, float wd, int op, int has_mom,
     LarsArgs lars) {
   static_assert(!(kLars && kTable), "LARS takes the gathered lists");
-  const int32_t* __restrict__ idx = lists.idx;
-  const void* __restrict__ val = lists.val;
   const int64_t stride = lists.stride;
   const int32_t* __restrict__ nnz = lists.nnz;
   const bool sparse_mode = op == kOpSparseSgd;
@@ -1962,26 +2199,28 @@ __global__ __launch_bounds__(kUBlock) void k_update(
   __syncthreads();
 
   // 1. accumulate every worker's entries that fall in this tile
+  const PairSrc<kTable> src{lists.idx, lists.val, stride, s_ip, s_vp};
   for (int p0 = 0; p0 < P; p0 += kUBlock) {
     const int p = p0 + tid;
-    int32_t b = 0, e = 0;
-    if (p < P) {
-      int64_t np;
-      if constexpr (kTable) {
-        const WorkerList wl = lists.table[p];
-        np = wl.n;
-        s_ip[tid] = wl.idx;
-        s_vp[tid] = static_cast<const float*>(wl.val);
-      } else {
-        np = nnz ? (int64_t)nnz[p] : stride;
-        np = np < 0 ? 0 : (np > stride ? stride : np);
+    // (the bounds and the worker's count are requested together)
+    const int pc = min(p, P - 1);
+    int64_t sb = seg[(int64_t)u * P + pc], se = seg[(int64_t)(u + 1) * P + pc];
+    int64_t np;
+    if constexpr (kTable) {
+      const WorkerList wl = lists.table[pc];
+      np = wl.n;
+      s_ip[tid] = wl.idx;
+      s_vp[tid] = static_cast<const float*>(wl.val);
+    } else {
+      np = stride;
+      if (nnz) {
+        const int64_t n = nnz[pc];
+        np = n < 0 ? 0 : (n > stride ? stride : n);
       }
-      int64_t sb = seg[(int64_t)u * P + p], se = seg[(int64_t)(u + 1) * P + p];
-      sb = sb < 0 ? 0 : (sb > np ? np : sb);
-      se = se < sb ? sb : (se > np ? np : se);
-      b = (int32_t)sb;
-      e = (int32_t)se;
     }
+    sb = sb < 0 ? 0 : (sb > np ? np : sb);
+    se = se < sb ? sb : (se > np ? np : se);
+    const int32_t b = (int32_t)sb, e = p < P ? (int32_t)se : b;
     sbeg[tid] = b;
     // inclusive prefix of the segment lengths, for the entry -> worker search
     // (block_scan ends with a barrier, so scan[] can be rewritten here)
@@ -1989,34 +2228,11 @@ __global__ __launch_bounds__(kUBlock) void k_update(
     const uint32_t ex = block_scan<kUBlock>((uint32_t)(e - b), scan, &total);
     scan[tid] = ex + (uint32_t)(e - b);
     __syncthreads();
-    // entries of this batch of workers, kPairUnroll per thread with all
-    // their loads in flight before the LDS adds
+    // entries of this batch of workers, kPairUnroll per thread
     for (uint32_t q0 = 0; q0 < total; q0 += kUBlock * kPairUnroll) {
       int32_t li[kPairUnroll];
       float vv[kPairUnroll];
-#pragma unroll
-      for (int j = 0; j < kPairUnroll; ++j) {
-        const uint32_t q = q0 + j * kUBlock + tid;
-        li[j] = -1;
-        vv[j] = 0.0f;
-        if (q < total) {
-          int lo = 0, hi = kUBlock - 1;
-          while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (scan[mid] > q) hi = mid; else lo = mid + 1;
-          }
-          const uint32_t before = lo ? scan[lo - 1] : 0u;
-          const int64_t jj = (int64_t)sbeg[lo] + (q - before);
-          if constexpr (kTable) {
-            li[j] = ((const gint*)s_ip[lo])[jj] - base;
-            vv[j] = ((const gfloat*)s_vp[lo])[jj];
-          } else {
-            const int64_t gi = (int64_t)(p0 + lo) * stride + jj;
-            li[j] = idx[gi] - base;
-            vv[j] = get_val(val, (size_t)gi, val16);
-          }
-        }
-      }
+      load_pairs<kTable>(src, scan, sbeg, p0, q0, total, base, val16, li, vv);
       if constexpr (kDet) {
         det_accumulate(li, vv, len, sparse_mode, acc, mask, dcnt, dq, dv, &dtop);
       } else {
@@ -2032,69 +2248,22 @@ __global__ __launch_bounds__(kUBlock) void k_update(
     __syncthreads();
   }
 
-  // 2a. LARS norms: per tensor of the tile, sum w^2 and G^2 (double) into
-  // its pair
+  // 2. the norms, the SGD (or LARS) step or the dense sums
+  UpdTile ut;
+  ut.u = u;
+  ut.base = base;
+  ut.len = len;
+  ut.t0 = t0;
+  ut.w = w_tile;
+  ut.b = b_tile;
+  ut.fast = fast;
   if (lnorm) {
-    const int32_t tl = fast ? t0 : min(tile_first[u + 1], ntens - 1);
-    for (int ti = t0; ti <= tl; ++ti) {
-      const UpdTensor tt = tens[ti];
-      const int64_t a = max((int64_t)base, tt.goff);
-      const int64_t z = min((int64_t)base + len, tt.goff + tt.n);
-      if (z <= a) continue;  // (uniform in the workgroup)
-      double sw = 0.0, sg = 0.0;
-      if (fast) {
-        const float4* a4 = reinterpret_cast<const float4*>(acc);
-#pragma unroll
-        for (int q = 0; q < kUVecPerThread; ++q) {
-          const float4 G = a4[q * kUBlock + tid];
-          const float4 w = wv[q];
-          sw += (double)w.x * w.x + (double)w.y * w.y + (double)w.z * w.z + (double)w.w * w.w;
-          sg += (double)G.x * G.x + (double)G.y * G.y + (double)G.z * G.z + (double)G.w * G.w;
-        }
-      } else {
-        const gfloat* w = gptr(tt.w + (a - tt.goff));
-        const int la = (int)(a - base), cnt = (int)(z - a);
-        for (int q = tid; q < cnt; q += kUBlock) {
-          const double wq = w[q], gq = acc[la + q];
-          sw += wq * wq;
-          sg += gq * gq;
-        }
-      }
-      const double2 r = ublock_sum2(sw, sg, lred);
-      if (tid == 0) lars.part[lars.tpair[ti] + (u - (int32_t)(tt.goff >> kUShift))] = r;
-    }
+    tile_norms(tens, tile_first, ntens, ut, wv, acc, lars, lred);
     return;
   }
-
-  // 2. apply the SGD (or LARS) step
   if (fast) {
-    float4* w4 = reinterpret_cast<float4*>(w_tile);
-    float4* b4 = reinterpret_cast<float4*>(b_tile);
-    const float4* a4 = reinterpret_cast<const float4*>(acc);
-#pragma unroll
-    for (int q = 0; q < kUVecPerThread; ++q) {
-      const int v = q * kUBlock + tid;
-      const float4 G = a4[v];
-      if (densify) {
-        store_nt4(w4 + v, G);
-        continue;
-      }
-      float4 w = wv[q], bb = mom ? bv[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-      if (lapply) {
-        const float rate = (float)lars.rate[t0];
-        w.x = lars_step(G.x, w.x, bb.x, mom, rate, mu, lars.eps);
-        w.y = lars_step(G.y, w.y, bb.y, mom, rate, mu, lars.eps);
-        w.z = lars_step(G.z, w.z, bb.z, mom, rate, mu, lars.eps);
-        w.w = lars_step(G.w, w.w, bb.w, mom, rate, mu, lars.eps);
-      } else {
-        w.x = sgd_step(G.x, w.x, bb.x, mom, lr, mu, wd);
-        w.y = sgd_step(G.y, w.y, bb.y, mom, lr, mu, wd);
-        w.z = sgd_step(G.z, w.z, bb.z, mom, lr, mu, wd);
-        w.w = sgd_step(G.w, w.w, bb.w, mom, lr, mu, wd);
-      }
-      store_nt4(w4 + v, w);
-      if (mom) store_nt4(b4 + v, bb);
-    }
+    const float rate = lapply ? (float)lars.rate[t0] : 0.0f;
+    tile_step_fast(ut, wv, bv, acc, densify, lapply, mom, rate, lr, mu, wd, lars.eps);
     return;
   }
   const int32_t t1 = min(tile_first[u + 1], ntens - 1);
@@ -2118,55 +2287,7 @@ __global__ __launch_bounds__(kUBlock) void k_update(
     }
     return;
   }
-  for (int ti = t0; ti < ntens; ++ti) {
-    const UpdTensor tt = tens[ti];
-    if (tt.goff >= (int64_t)base + len) break;
-    const int64_t a = max((int64_t)base, tt.goff);
-    const int64_t z = min((int64_t)base + len, tt.goff + tt.n);
-    if (z <= a) continue;
-    const int cnt = (int)(z - a);
-    const int la = (int)(a - base);
-    gfloat* __restrict__ w = gptr(tt.w + (a - tt.goff));
-    gfloat* __restrict__ bm = mom ? gptr(tt.b + (a - tt.goff)) : nullptr;
-    const bool vec = ((reinterpret_cast<uintptr_t>(w) |
-                       (bm ? reinterpret_cast<uintptr_t>(bm) : 0u)) & 15u) == 0;
-    const float rate = lapply ? (float)lars.rate[ti] : 0.0f;
-    auto step = [&](float G, float wq, float& bq) -> float {
-      return lapply ? lars_step(G, wq, bq, mom, rate, mu, lars.eps)
-                    : sgd_step(G, wq, bq, mom, lr, mu, wd);
-    };
-    int done = 0;
-    if (vec) {
-      const int nv = cnt >> 2;
-      gv4f* w4 = (gv4f*)w;
-      gv4f* b4 = (gv4f*)bm;
-      for (int q = tid; q < nv; q += kUBlock) {
-        if (densify) {
-          const int l = la + 4 * q;
-          w4[q] = v4f{acc[l], acc[l + 1], acc[l + 2], acc[l + 3]};
-          continue;
-        }
-        const v4f wv4 = w4[q];
-        const v4f bv4 = bm ? b4[q] : v4f{0.f, 0.f, 0.f, 0.f};
-        float wq[4] = {wv4.x, wv4.y, wv4.z, wv4.w}, bq[4] = {bv4.x, bv4.y, bv4.z, bv4.w};
-        const int l = la + 4 * q;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) wq[c] = step(acc[l + c], wq[c], bq[c]);
-        w4[q] = v4f{wq[0], wq[1], wq[2], wq[3]};
-        if (mom) b4[q] = v4f{bq[0], bq[1], bq[2], bq[3]};
-      }
-      done = nv << 2;
-    }
-    for (int q = done + tid; q < cnt; q += kUBlock) {
-      if (densify) {
-        w[q] = acc[la + q];
-        continue;
-      }
-      float bq = mom ? bm[q] : 0.0f;
-      w[q] = step(acc[la + q], w[q], bq);
-      if (mom) bm[q] = bq;
-    }
-  }
+  tile_step_general(tens, ntens, ut, acc, densify, lapply, mom, lr, mu, wd, lars);
 }
 
 // ---------------------------------------------------------------------------

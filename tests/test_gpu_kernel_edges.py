@@ -22,12 +22,12 @@ def orc():
 
 
 # Ordered sums: (workers, entries per worker, distinct positions of the first
-# tile they fall on). 1,024 entries are one chunk of a tile's accumulation:
-# all at one position, just over a chunk, pairs only (512 runs), every
-# position of a pair of counter halves, and all entries alone.
-@pytest.mark.parametrize("P,k,pool", [(1, 1024, 1), (1024, 1, 1), (205, 5, 1), (2, 512, 512),
-                                      (3, 341, 341), (16, 64, 65), (1, 1024, 1024), (300, 7, 8),
-                                      (2, 1, 2)])
+# tile they fall on). 768 entries are one chunk of a tile's accumulation: all
+# at one position, just over a chunk, pairs only (as many runs as there can
+# be), positions in both counter halves, all entries alone, several chunks.
+@pytest.mark.parametrize("P,k,pool", [(1, 768, 1), (769, 1, 1), (205, 5, 1), (2, 384, 384),
+                                      (3, 256, 256), (16, 64, 65), (1, 768, 768), (300, 7, 8),
+                                      (2, 1, 2), (128, 32, 700)])
 @pytest.mark.parametrize("mode", ["plain", "momentum"])
 def test_ordered_chunks(P, k, pool, mode):
     rng = np.random.default_rng([P, k, pool])
