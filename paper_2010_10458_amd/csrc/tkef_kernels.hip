@@ -144,6 +144,17 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* wsum, uint3
 typedef __attribute__((address_space(1))) float gfloat;
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) v4f gv4f;
+// Four floats that need only start on a 4-byte boundary: gfx950's 16-byte
+// global loads and stores take any dword address. A tensor that starts off the
+// 16-byte grid (a shard of a flat buffer) is then read and written a
+// wavefront's 1,024 contiguous bytes at a time; with 4-byte accesses two of
+// the three lines that a wavefront's store touched were partial ones.
+// (One tensor starting 4 bytes off, k_stream: 3.2 M elements 13.3 -> 11.8 us,
+// 2^25 85.6 -> 70.9, 2^27 351 -> 271 and 340 M 948 -> 667, the last two
+// with the three workgroups per compute unit of large inputs; k_collect at 340 M
+// 157 -> 106 us, at 3.2 M 8.4 -> 7.7.)
+typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
+typedef __attribute__((address_space(1))) v4fu gv4fu;
 __device__ __forceinline__ const gfloat* gptr(const float* p) { return (const gfloat*)p; }
 __device__ __forceinline__ gfloat* gptr(float* p) { return (gfloat*)p; }
 
@@ -152,11 +163,11 @@ __device__ __forceinline__ gfloat* gptr(float* p) { return (gfloat*)p; }
 __device__ __forceinline__ void load_line(const float* __restrict__ x, int e0, int n,
                                           float (&v)[kLine]) {
   const float* p = x + e0;
-  if (n == kLine && (reinterpret_cast<uintptr_t>(p) & 15u) == 0) {
-    const gv4f* p4 = (const gv4f*)p;
+  if (n == kLine) {
+    const gv4fu* p4 = (const gv4fu*)p;
 #pragma unroll
     for (int q = 0; q < kLine / 4; ++q) {
-      const v4f f = p4[q];
+      const v4fu f = p4[q];
       v[4 * q + 0] = f.x;
       v[4 * q + 1] = f.y;
       v[4 * q + 2] = f.z;
@@ -236,6 +247,16 @@ __device__ __forceinline__ void store_nt4(float4* p, float4 v) {
   __builtin_nontemporal_store(t, (gv4f*)p);
 }
 
+// The same at any 4-byte address, four floats from p.
+__device__ __forceinline__ float4 load_nt4u(const float* p) {
+  const v4fu t = __builtin_nontemporal_load((const gv4fu*)p);
+  return make_float4(t.x, t.y, t.z, t.w);
+}
+__device__ __forceinline__ void store_nt4u(float* p, float4 v) {
+  const v4fu t = {v.x, v.y, v.z, v.w};
+  __builtin_nontemporal_store(t, (gv4fu*)p);
+}
+
 __device__ __forceinline__ uint32_t add_quad(float4 a, float4 b, float4& x, uint32_t* h) {
   x.x = a.x + b.x;
   x.y = a.y + b.y;
@@ -297,23 +318,19 @@ __global__ __launch_bounds__(kBlock) void k_stream(const TileDesc* __restrict__ 
     float* __restrict__ r = t.r + s0;
     uint16_t* __restrict__ sq = summ + (size_t)(unit / (kTile / kQuarter)) * kLinesPerTile +
                                 s0 / kLine;
-    const bool full = len == kQuarter &&
-        ((reinterpret_cast<uintptr_t>(g) | reinterpret_cast<uintptr_t>(r)) & 15u) == 0;
-    if (full) {
+    if (len == kQuarter) {
       // kQV float4 of g and of r per thread, all loads in flight together; a
       // line is 8 consecutive lanes
-      const float4* __restrict__ g4 = reinterpret_cast<const float4*>(g);
-      float4* __restrict__ r4 = reinterpret_cast<float4*>(r);
       float4 a[kQV], b[kQV];
 #pragma unroll
-      for (int v = 0; v < kQV; ++v) a[v] = load_nt4(g4 + v * kBlock + tid);
+      for (int v = 0; v < kQV; ++v) a[v] = load_nt4u(g + 4 * (v * kBlock + tid));
 #pragma unroll
-      for (int v = 0; v < kQV; ++v) b[v] = load_nt4(r4 + v * kBlock + tid);
+      for (int v = 0; v < kQV; ++v) b[v] = load_nt4u(r + 4 * (v * kBlock + tid));
 #pragma unroll
       for (int v = 0; v < kQV; ++v) {
         float4 x;
         uint32_t m = add_quad(a[v], b[v], x, h);
-        store_nt4(r4 + v * kBlock + tid, x);
+        store_nt4u(r + 4 * (v * kBlock + tid), x);
         tmax = max(tmax, m);
         m = max(m, (uint32_t)__shfl_xor((int)m, 1));
         m = max(m, (uint32_t)__shfl_xor((int)m, 2));
@@ -321,9 +338,9 @@ __global__ __launch_bounds__(kBlock) void k_stream(const TileDesc* __restrict__ 
         if ((tid & 7) == 0) sq[(v * kBlock + tid) >> 3] = (uint16_t)(m >> 16);
       }
     } else {
-      // partial or misaligned quarter: element by element (coalesced 4-byte
-      // accesses), every load issued before the first use so the quarter
-      // costs one memory latency. Element e = q * kBlock + tid: a wavefront's
+      // partial quarter: element by element (coalesced 4-byte accesses), every
+      // load issued before the first use so the quarter costs one memory
+      // latency. Element e = q * kBlock + tid: a wavefront's
       // 64 lanes hold two whole lines, so a line's maximum key is a
       // reduction over 32 lanes (lanes past the end contribute 0); the
       // summary of a line without elements is not written.
@@ -2754,16 +2771,12 @@ __global__ __launch_bounds__(kBlock) void k_ms_stream(const TileDesc* __restrict
     float* __restrict__ r = t.r + s0;
     uint16_t* __restrict__ sq = summ + (size_t)(unit / (kTile / kQuarter)) * kLinesPerTile +
                                 s0 / kLine;
-    const bool full = len == kQuarter &&
-        ((reinterpret_cast<uintptr_t>(g) | reinterpret_cast<uintptr_t>(r)) & 15u) == 0;
-    if (full) {
-      const float4* __restrict__ g4 = reinterpret_cast<const float4*>(g);
-      float4* __restrict__ r4 = reinterpret_cast<float4*>(r);
+    if (len == kQuarter) {
       float4 a[kQV], b[kQV];
 #pragma unroll
-      for (int v = 0; v < kQV; ++v) a[v] = load_nt4(g4 + v * kBlock + tid);
+      for (int v = 0; v < kQV; ++v) a[v] = load_nt4u(g + 4 * (v * kBlock + tid));
 #pragma unroll
-      for (int v = 0; v < kQV; ++v) b[v] = load_nt4(r4 + v * kBlock + tid);
+      for (int v = 0; v < kQV; ++v) b[v] = load_nt4u(r + 4 * (v * kBlock + tid));
 #pragma unroll
       for (int v = 0; v < kQV; ++v) {
         float4 x;
@@ -2771,7 +2784,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_stream(const TileDesc* __restrict
         x.y = a[v].y + b[v].y;
         x.z = a[v].z + b[v].z;
         x.w = a[v].w + b[v].w;
-        store_nt4(r4 + v * kBlock + tid, x);
+        store_nt4u(r + 4 * (v * kBlock + tid), x);
         const uint32_t k0 = mag_key(x.x), k1 = mag_key(x.y), k2 = mag_key(x.z), k3 = mag_key(x.w);
         ms_accum(k0, es);
         ms_accum(k1, es);
@@ -2785,8 +2798,8 @@ __global__ __launch_bounds__(kBlock) void k_ms_stream(const TileDesc* __restrict
         if ((tid & 7) == 0) sq[(v * kBlock + tid) >> 3] = (uint16_t)(m >> 16);
       }
     } else {
-      // partial or misaligned quarter, as in k_stream: element by element,
-      // line maxima reduced over the 32 lanes that hold each line
+      // partial quarter, as in k_stream: element by element, line maxima
+      // reduced over the 32 lanes that hold each line
       constexpr int kPer = kQuarter / kBlock;
       float gv[kPer], rv[kPer];
 #pragma unroll
@@ -2884,13 +2897,12 @@ __global__ __launch_bounds__(kBlock) void k_ms_count(
         const TileDesc t = tiles[tile];
         len[q] = s0 < t.len ? min(kQuarter, t.len - s0) : 0;
         xs[q] = t.r + s0;
-        full[q] = len[q] == kQuarter && (reinterpret_cast<uintptr_t>(xs[q]) & 15u) == 0;
+        full[q] = len[q] == kQuarter;
         if (full[q]) {
-          const float4* x4 = reinterpret_cast<const float4*>(xs[q]);
 #pragma unroll
           for (int v = 0; v < kQV; ++v) {
             const int i4 = v * kBlock + tid;  // float4 index: line i4 / 8
-            f[q][v] = (sv[v] >= smin) ? load_nt4(x4 + i4) : make_float4(0.f, 0.f, 0.f, 0.f);
+            f[q][v] = (sv[v] >= smin) ? load_nt4u(xs[q] + 4 * i4) : make_float4(0.f, 0.f, 0.f, 0.f);
           }
         }
       }

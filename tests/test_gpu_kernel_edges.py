@@ -43,3 +43,53 @@ def test_ordered_chunks(P, k, pool, mode):
     lr, mu, wd = (0.1, 0.9, 5e-5) if mode == "momentum" else (0.1, 0.0, 0.0)
     det_update_vs_oracle([d], w0, b0, idx.astype(np.int32), val, lr, mu, wd,
                          label=f"chunk edges pool={pool} {mode}")
+
+
+# Tensors that start off the 16-byte grid, gradient and residual each on its
+# own: whole 2,048-element units, remainders, single lines, two tensors. The
+# elements around each tensor keep their values.
+@pytest.mark.parametrize("mode", ["global", "tensor", "approx"])
+@pytest.mark.parametrize("gs,rs", [(1, 1), (2, 2), (3, 3), (0, 1), (1, 0), (3, 2)])
+def test_sparsify_off_grid(gs, rs, mode):
+    import torch
+    import oracle.mstopk as mstopk
+    dev = need_gpu()
+    sizes = [3 * 8192 + 2048 + 37, 2048, 4097, 31, 33]
+    announce(f"sparsify off grid g+{gs} r+{rs} {mode}")
+    rng = np.random.default_rng([gs, rs])
+    grads = [rng.standard_normal(n).astype(np.float32) for n in sizes]
+    res = [(rng.standard_normal(n) * 0.5).astype(np.float32) for n in sizes]
+    guard = np.float32(1e30)
+
+    def place(arrs, shift):
+        bufs = []
+        for a in arrs:
+            b = np.full(a.size + 16, guard, np.float32)
+            b[shift:shift + a.size] = a
+            bufs.append(torch.from_numpy(b).to(dev))
+        return bufs, [b[shift:shift + a.size] for b, a in zip(bufs, arrs)]
+
+    gb, g = place(grads, gs)
+    rb, r = place(res, rs)
+    m = {"global": tk.GLOBAL, "tensor": tk.PER_TENSOR, "approx": tk.APPROX}[mode]
+    status = torch.zeros(1, dtype=torch.int32, device=dev)
+    plan = tk.SparsifyPlan(sizes, mode=m, rho=0.01).bind(g, r)
+    idx, val = plan.execute(status=status, **({"window_word": 12345} if mode == "approx" else {}))
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    if mode == "approx":
+        k = tk.k_from_rho(sum(sizes), 0.01)
+        oi, ov, flat, _ = mstopk.mstopk_sparsify(gen.concat(grads), gen.concat(res), k, 30,
+                                                  12345)
+        orr = np.split(flat, np.cumsum(sizes)[:-1])
+    else:
+        oi, ov, orr, _ = orc().sparsify(grads, res, rho=0.01,
+                                        mode=oracle.GLOBAL if mode == "global" else oracle.PER_TENSOR)
+    assert_bitwise(idx.cpu().numpy(), oi, "idx")
+    assert_bitwise(val.cpu().numpy(), ov, "val")
+    for t, n in enumerate(sizes):
+        got = rb[t].cpu().numpy()
+        assert_bitwise(got[rs:rs + n], np.asarray(orr[t]).ravel(), f"residual[{t}]")
+        assert (got[:rs] == guard).all() and (got[rs + n:] == guard).all()
+        back = gb[t].cpu().numpy()
+        assert_bitwise(back[gs:gs + n], grads[t], f"gradient[{t}]")
