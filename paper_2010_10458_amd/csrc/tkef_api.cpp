@@ -403,15 +403,37 @@ hipError_t run_one_group(const tkef_sparsify_plan_s* p, char* base, char* zb,
   return e;
 }
 
-// Persistent stream grid: four workgroups per compute unit.
-int stream_grid_for(int64_t ntiles, int32_t* grid, int32_t* cus_out) {
+// Persistent stream grid: four workgroups per compute unit, or three for large
+// inputs, above kStreamFewUnits units. With exactly three the three streams (g,
+// r, and r back) reach HBM at a higher rate: 340 M elements 745 -> 621 us (6.57
+// TB/s), 110 M 229 -> 214, 2^26 135 -> 130; 704, 736, 800, 832 or 896 workgroups
+// on 256 compute units are all slower than 768 (648-756 us at 340 M). Below
+// that size the rounds of units are too few for it to show (2^25: 67 -> 69 us)
+// and a fourth workgroup shortens the ends (3.2 M: 11.8 against 12.7 us). A
+// workgroup adds its histogram to the group's whenever the group changes, and
+// waits for that; where most units bring such a change (many tensors of a few
+// hundred units, each a group) the fourth workgroup covers the wait (60 M over
+// 300 tensors: 127 against 138 us), so three also need the changes, at most
+// min(units, workgroups) per group, to be no more than half of the units.
+constexpr int64_t kStreamFewUnits = 24576;
+int stream_grid_for(const tkef_sparsify_plan_s* p, int32_t* grid, int32_t* cus_out) {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       cus <= 0)
     return TKEF_EHIP;
-  const int64_t units = ntiles * (kTile / kStreamUnit);
-  *grid = (int32_t)std::min<int64_t>((int64_t)4 * cus, units);
+  const int64_t units = (int64_t)p->ntiles * (kTile / kStreamUnit);
+  int64_t per_cu = 4;
+  if (units > kStreamFewUnits) {
+    const int64_t few = (int64_t)3 * cus;
+    int64_t changes = few;
+    if (p->ngroups > 1) {
+      changes = 0;
+      for (int64_t n : p->numels) changes += std::min<int64_t>(few, (n + kStreamUnit - 1) / kStreamUnit);
+    }
+    if (2 * changes <= units) per_cu = 3;
+  }
+  *grid = (int32_t)std::min<int64_t>(per_cu * cus, units);
   if (cus_out) *cus_out = cus;
   return TKEF_OK;
 }
@@ -437,7 +459,7 @@ extern "C" int tkef_sparsify_plan_bind(tkef_sparsify_plan plan, const float* con
     }
   }
   int32_t cus = 0;
-  if (stream_grid_for(plan->ntiles, &plan->stream_grid, &cus)) return TKEF_EHIP;
+  if (stream_grid_for(plan, &plan->stream_grid, &cus)) return TKEF_EHIP;
   const int64_t units = (int64_t)plan->ntiles * (kTile / kStreamUnit);
   plan->count_grid = (int32_t)std::max<int64_t>(1, std::min<int64_t>((int64_t)8 * cus, (units + 1) / 2));
   // two candidate workgroups per compute unit are all resident at once
@@ -702,7 +724,7 @@ extern "C" int tkef_sparsify1_static(const float* g, float* r, int64_t d, int64_
   p.nlines = (int64_t)p.ntiles * kLinesPerTile;
   if (!sparsify_layout(&p)) return TKEF_ERANGE;
   if (p.ws_bytes > kStaticScratchBytes) return TKEF_EWORKSPACE;  // (not within the limits)
-  if (stream_grid_for(p.ntiles, &p.stream_grid, nullptr)) return TKEF_EHIP;
+  if (stream_grid_for(&p, &p.stream_grid, nullptr)) return TKEF_EHIP;
   hipError_t e = hipSuccess;
   char* base = static_cast<char*>(static_scratch(&e));
   if (!base) return TKEF_EHIP;
