@@ -139,8 +139,9 @@ struct tkef_sparsify_plan_s {
   std::vector<GroupDesc> groups;
   uint32_t cand_cap = 0;  // per-tensor path: capacity of the compacted candidate list
   uint32_t rcap = 0;      // one-group path: candidates stored per region
-  int32_t sel_lpt = 1, sel_grid = 1, sel_block = 1;  // selection kernels: lines per thread,
-                                                    // workgroups, threads per workgroup
+  // selection kernels: lines per thread, lines per workgroup, workgroups, threads
+  // per workgroup
+  int32_t sel_lpt = 1, sel_rl = 1, sel_grid = 1, sel_block = 1;
   // Scratch that must start at zero (histograms, prefix flags, overflow and
   // count words), at off_zero; offsets below are relative to it. It is laid
   // out so that what the execution's last kernel uses comes last, from
@@ -185,7 +186,7 @@ bool sparsify_layout(tkef_sparsify_plan_s* p) {
   const bool one = p->ngroups == 1;
   const bool approx = p->mode == TKEF_APPROX;
   const bool coll = one && !approx;
-  const int64_t sb = coll ? collect_block(p->nlines, p->k_total, p->d) : select_block();
+  const int64_t sb = coll ? collect_block(p->nlines) : select_block();
   p->sel_block = (int32_t)sb;
   const int64_t sg = select_max_groups();
   const int64_t want = (p->nlines + sb * 256 - 1) / (sb * 256);
@@ -193,7 +194,15 @@ bool sparsify_layout(tkef_sparsify_plan_s* p) {
   while (lpt < want && lpt < select_max_lpt()) lpt *= 2;
   if ((p->nlines + sb * lpt - 1) / (sb * lpt) > sg) return false;  // (kMaxTiles)
   p->sel_lpt = (int32_t)lpt;
-  const int64_t g_lines = (p->nlines + sb * lpt - 1) / (sb * lpt);
+  // one exact group: collect_regions() equal regions, of no fewer lines than
+  // four per thread
+  int64_t rl = sb * lpt;
+  if (coll) {
+    const int64_t even = (p->nlines + collect_regions() - 1) / collect_regions();
+    rl = std::max<int64_t>((even + lpt - 1) / lpt * lpt, sb * 4);
+  }
+  p->sel_rl = (int32_t)rl;
+  const int64_t g_lines = (p->nlines + rl - 1) / rl;
   // Candidates are the positions at or above the level-1 threshold bin:
   // about k plus one bin's worth. One group: each region (the lines of one
   // workgroup) stores up to rcap of them, several times the even share of
@@ -203,7 +212,7 @@ bool sparsify_layout(tkef_sparsify_plan_s* p) {
   // 4k + 65536. Heavier inputs fall back to re-reading lines.
   if (one) {
     p->sel_grid = (int32_t)std::max<int64_t>(1, g_lines);
-    const int64_t region = lpt * sb * kLine;
+    const int64_t region = rl * kLine;
     const int64_t share = (8 * p->k_total + 65536 + p->sel_grid - 1) / p->sel_grid;
     p->rcap = (uint32_t)std::min<int64_t>(
         region, std::max<int64_t>(std::max<int64_t>(4096, (share + 63) / 64 * 64), region / 64));
@@ -393,11 +402,11 @@ hipError_t run_one_group(const tkef_sparsify_plan_s* p, char* base, char* zb,
   hipError_t e = launch_stream(tiles, p->ntiles, p->stream_grid, hist1, p->nslots, summ, status,
                                stream_clear, stream_words, s, tr.at(0));
   if (e == hipSuccess)
-    e = launch_collect(tiles, groups, st, hist1, p->nslots, summ, nl, lpt, sg, p->sel_block,
-                       p->rcap, hist2, rbin, rcand, rband, rbtmp, rsuf, rcnt, s, tr.at(1));
+    e = launch_collect(tiles, groups, st, hist1, p->nslots, summ, nl, lpt, p->sel_rl, sg,
+                       p->sel_block, p->rcap, hist2, rbin, rcand, rband, rbtmp, rsuf, rcnt, s, tr.at(1));
   if (e == hipSuccess)
-    e = launch_finish(tiles, groups, st, summ, nl, lpt, sg, p->sel_block, p->rcap, hist2, rbin,
-                      rcand, rband, rsuf, rcnt, idx_out, val_out, val16, clear_next, clear_words,
+    e = launch_finish(tiles, groups, st, summ, nl, lpt, p->sel_rl, sg, p->sel_block, p->rcap, hist2,
+                      rbin, rcand, rband, rsuf, rcnt, idx_out, val_out, val16, clear_next, clear_words,
                       reinterpret_cast<uint32_t*>(zb + p->off_ticket),
                       reinterpret_cast<uint32_t*>(base + p->off_rzr), s, tr.at(2));
   return e;

@@ -490,20 +490,13 @@ constexpr int kSWaves = kSBlock / 64;
 // workgroup, with more lines per thread, for inputs of up to kCSmallLines
 // summary lines: their per-thread steps (summaries, scans, bins) are short
 // instruction runs over every thread of a region, so fewer threads per
-// compute unit finish them sooner. Larger inputs take kSBlock threads, whose
-// regions hold more flagged lines, so each thread walks fewer of them;
-// except dense selections (k >= d / kCDenseDiv), whose many flagged lines
-// are walked faster by two half-size workgroups per compute unit, one
-// loading its lines while the other works through its own (110 M
-// elements: 375 against 387 us at rho = 0.01, 342 against 347 at 0.007, even
-// at 0.005, 8-10 us slower at 0.002-0.004), as long as the half-size
-// regions number at most kCDenseMaxGroups: every finish workgroup's work
-// grows with the number of regions (340 M elements, 1,297 regions: 1,372
-// against 1,310 us at rho = 0.01).
+// compute unit finish them sooner (25.6 M elements, collect and finish: 8.2 +
+// 6.9 against 9.4 + 8.6 us with kSBlock threads). Larger inputs take kSBlock
+// threads, whose regions hold more flagged lines (110 M, rho = 0.001: 18.6 +
+// 10.2 against 24.9 + 10.9 us; rho = 0.01: 69.7 + 30.0 against 74.2 + 31.0;
+// 340 M at 0.01: 265 + 114 against 251 + 119).
 constexpr int kCBlockSmall = 512;
 constexpr int64_t kCSmallLines = (int64_t)256 * kCBlockSmall * 8;
-constexpr int64_t kCDenseDiv = 160;
-constexpr int64_t kCDenseMaxGroups = 512;
 constexpr int kSMaxGroups = 4096;
 constexpr int kSMaxLpt = 16;     // lines per thread at most
 static_assert(kLinesPerTile % kSMaxLpt == 0, "a thread's lines lie in one tile");
@@ -665,7 +658,7 @@ struct LineSpan {
   __device__ __forceinline__ void load(const TileDesc* __restrict__ tiles,
                                        const uint16_t* __restrict__ summ, int64_t nlines,
                                        int64_t l0, int lpt) {
-    const bool has = l0 < nlines;  // nlines is a multiple of kLinesPerTile
+    const bool has = l0 < nlines;  // (l0 and nlines are multiples of lpt)
     tile = has ? (int)(l0 / kLinesPerTile) : 0;
     e0 = (int)(l0 % kLinesPerTile) * kLine;
     // four summaries per 8-byte load (l0 and lpt are multiples of 4)
@@ -752,14 +745,29 @@ __device__ __forceinline__ void walk_cands(const TileDesc* __restrict__ tiles, i
 // ---------------------------------------------------------------------------
 // One selection group (top-k over all tensors together): collect, finish.
 //
-// Workgroup w of either kernel (NT threads) owns the region of summary lines
-// [w * NT * lpt, (w + 1) * NT * lpt), lpt consecutive lines per thread. No workgroup waits on another: the ordered output is placed from
-// small per-region counts that collect leaves behind.
+// Workgroup w of either kernel (NT threads) owns the region of rl summary lines
+// from w * rl on (rl a multiple of lpt), taken in blocks of NT * lpt lines, lpt
+// consecutive ones per thread. The lines are split into at most kFMaxGroups
+// equal regions, one per compute unit: every finish workgroup reads the counts
+// of all regions, and the fixed work of a workgroup (the picks, the level-2
+// tables) is done once per compute unit, without a second round of
+// workgroups (340 M elements, collect and finish: 649 regions of 16 lines per
+// thread 85 + 47 us, 217 of three such blocks 72 + 22; 110 M at rho = 0.01: 424
+// regions, of which some compute units had two and some one, 74 + 30 us).
+// No workgroup waits on another: the ordered output is placed from small
+// per-region counts that collect leaves behind.
 //
 // collect makes the level-1 pick (bin B1 of the k-th largest key) itself from
 // the slotted histogram. The region's flagged lines (summary >= B1 << 20) are
-// listed in LDS in position order and read one line per thread, all in one
-// round. It writes
+// listed in LDS in position order and read in rounds of a line to two threads,
+// eight lanes to a line at a time (one lane to a line asks the L1 for the line eight
+// times). A round lists its candidates in LDS, in position order; they are
+// then taken one per thread while the next round's lines are on their way.
+// (Before, each thread read a line and worked through its candidates, picked
+// from registers. collect, before and now, regions and rounds together: 256 K
+// elements 7.6 -> 6.7 us, 3.2 M 7.7 -> 6.7, 25.6 M 9.2 -> 8.2, 110 M 74 -> 70 at
+// rho = 0.01, 340 M 85 -> 67.)
+// It writes
 //   rcand[w]    the candidates (key >= B1 << 20) in position order, as
 //               {global index, bits of x, address of the residual element};
 //   rband[w]    the keys of the band members (key >> 20 == B1), ordered by
@@ -784,12 +792,14 @@ __device__ __forceinline__ void walk_cands(const TileDesc* __restrict__ tiles, i
 // its own are the non-band candidates, the band members above bin B2 and the
 // bin-B2 members above T; the elements equal to T are bin-B2 members. From
 // these counts workgroup w places its region's selection.
-constexpr int kOvWords = kSMaxGroups / 32;
-constexpr int kFlCap = 4096;     // flagged lines listed in LDS at a time
+constexpr int kFMaxGroups = 256;  // regions at most
+constexpr int kOvWords = kFMaxGroups / 32;
+constexpr int kFlCap = 2048;     // flagged lines listed in LDS at a time
+constexpr int kSteps = 4;        // lines of a round: kSteps per eight threads
 constexpr int kBandCap = 4096;   // band members of a region kept in LDS
 constexpr int kC2Cap = 4096;     // level-2 class members kept in LDS by finish
 static_assert(kPerBin == 4, "rbin entries are read as one uint4");
-static_assert(kSMaxGroups <= 65536, "region numbers fit 16 bits");
+static_assert(kFMaxGroups <= kCBlockSmall, "one region per thread of finish");
 
 // (The sizes come last among the arguments: they are used at the start, so
 // both cache lines of the argument block are fetched then, and later reloads
@@ -801,7 +811,7 @@ __global__ __launch_bounds__(NT, 4) void k_collect(
     const uint16_t* __restrict__ summ, uint32_t* __restrict__ hist2,
     uint32_t* __restrict__ rbin, uint4* __restrict__ rcand, uint32_t* __restrict__ rband,
     uint32_t* __restrict__ rbtmp, uint32_t* __restrict__ rsuf, uint2* __restrict__ rcnt,
-    uint32_t rcap, int lpt, int64_t nlines) {
+    uint32_t rcap, int lpt, int32_t rl, int64_t nlines) {
   __shared__ uint32_t h[kH2Bins];
   __shared__ uint32_t hoff[kH2Bins];
   __shared__ uint32_t wsum[2 * (NT / 64)];
@@ -809,6 +819,10 @@ __global__ __launch_bounds__(NT, 4) void k_collect(
   __shared__ float* lptr[kFlCap];        // flagged lines: first element
   __shared__ uint32_t lgidx[kFlCap];     // global index of the first element
   __shared__ uint8_t lnum[kFlCap];       // elements in the line
+  // candidates of a round: line in the list * kLine + element
+  constexpr int kPerRound = NT / 8 * kSteps;
+  static_assert(kFlCap * kLine <= 65536, "a candidate's line and element fit 16 bits");
+  __shared__ uint16_t lcode[kPerRound * kLine];
   __shared__ uint32_t bandk[kBandCap];
   __shared__ uint32_t nband;
   const int tid = threadIdx.x, w = blockIdx.x;
@@ -818,7 +832,8 @@ __global__ __launch_bounds__(NT, 4) void k_collect(
   // summaries of this thread's lines (independent of the pick), then the
   // level-1 pick, whose barriers also publish the cleared LDS
   LineSpan ls;
-  ls.load(tiles, summ, nlines, ((int64_t)w * NT + tid) * lpt, lpt);
+  const int64_t rend = min(nlines, (int64_t)(w + 1) * rl);  // the region's lines end here
+  ls.load(tiles, summ, rend, (int64_t)w * rl + tid * lpt, lpt);
   __builtin_amdgcn_sched_barrier(0);  // keep those loads ahead of the histogram's
   const uint32_t k = groups[0].k;
   block_pick<NT, kH1Bins, kSlotsOne>(hist1, k, wsum, res);
@@ -826,83 +841,166 @@ __global__ __launch_bounds__(NT, 4) void k_collect(
   const uint32_t above1 = res[1];
   const uint32_t lo = B1 << kH1Shift;
 
-  // flagged lines in position order: thread order, then line order
-  const uint32_t mask = ls.flagged([&](int) -> uint32_t { return lo; });
-  uint32_t F;
-  const uint32_t fex = block_scan<NT>((uint32_t)__popc(mask), wsum, &F);
   uint32_t cw = 0u;   // candidates so far (workgroup-uniform)
   bool fits = true;   // workgroup-uniform
   uint4* __restrict__ cdst = rcand + (size_t)w * rcap;
 #pragma unroll 1
-  for (uint32_t c0 = 0; c0 < F; c0 += kFlCap) {
-    uint32_t m = mask, rank = fex;
+  for (int32_t s0 = 0; s0 < rl; s0 += NT * lpt) {
+    if (s0) ls.load(tiles, summ, rend, (int64_t)w * rl + s0 + tid * lpt, lpt);
+    // flagged lines in position order: thread order, then line order
+    const uint32_t mask = ls.flagged([&](int) -> uint32_t { return lo; });
+    uint32_t F;
+    const uint32_t fex = block_scan<NT>((uint32_t)__popc(mask), wsum, &F);
 #pragma unroll 1
-    while (m) {
-      const int q = __ffs(m) - 1;
-      m &= m - 1u;
-      if (rank >= c0 && rank < c0 + (uint32_t)kFlCap) {
-        const TileDesc& t = ls.t;
-        const int e0 = ls.e0_of(q);
-        lptr[rank - c0] = t.r + e0;
-        lgidx[rank - c0] = (uint32_t)(t.gstart + e0);
-        lnum[rank - c0] = (uint8_t)max(0, min(kLine, t.len - e0));
+    for (uint32_t c0 = 0; c0 < F; c0 += kFlCap) {
+      uint32_t m = mask, rank = fex;
+#pragma unroll 1
+      while (m) {
+        const int q = __ffs(m) - 1;
+        m &= m - 1u;
+        if (rank >= c0 && rank < c0 + (uint32_t)kFlCap) {
+          const TileDesc& t = ls.t;
+          const int e0 = ls.e0_of(q);
+          lptr[rank - c0] = t.r + e0;
+          lgidx[rank - c0] = (uint32_t)(t.gstart + e0);
+          lnum[rank - c0] = (uint8_t)max(0, min(kLine, t.len - e0));
+        }
+        ++rank;
       }
-      ++rank;
-    }
-    __syncthreads();
-    const uint32_t nl = min((uint32_t)kFlCap, F - c0);
-#pragma unroll 1
-    for (uint32_t b0 = 0; b0 < nl; b0 += NT) {
-      const uint32_t i = b0 + tid;
-      float v[kLine];
-      uint32_t hm = 0u, bm = 0u, gidx0 = 0u;  // candidates, band members of the line
-      float* rp = nullptr;
-      if (i < nl) {
-        gidx0 = lgidx[i];
-        rp = lptr[i];
-        const int n = lnum[i];
-        load_line(rp, 0, n, v);
+      __syncthreads();
+      const uint32_t nl = min((uint32_t)kFlCap, F - c0);
+      // A wavefront takes 32 lines of a round: in step q of four, lines 8 q ..
+      // 8 q + 7 of them, eight lanes to a line.
+      const int lane = tid & 63, e = (lane & 7) * 4;
+      float4 v[kSteps];
+      auto line_of = [&](uint32_t b0, int q) -> uint32_t {
+        return b0 + (uint32_t)((tid >> 6) * 8 * kSteps + 8 * q + (lane >> 3));
+      };
+      uint32_t vm = 0u;  // bit 4 q + j: element e + j of step q's line exists
+      // All loads are issued without a branch between them: a lane whose
+      // four elements are not all there reads the tile table instead, and its
+      // elements one by one afterwards (a line is partial at the end of a
+      // tensor only); lines past the last repeat it.
+      auto fetch = [&](uint32_t b0) {
+        vm = 0u;
+        if (b0 + (tid >> 6) * 8u * kSteps >= nl) return;
+        bool part = false;
 #pragma unroll
-        for (int j = 0; j < kLine; ++j) {
-          const uint32_t key = mag_key(v[j]);
-          hm |= (j < n && key >= lo) ? (1u << j) : 0u;
-          bm |= (j < n && (key >> kH1Shift) == B1) ? (1u << j) : 0u;
+        for (int q = 0; q < kSteps; ++q) {
+          const uint32_t i = line_of(b0, q), ic = min(i, nl - 1u);
+          const int n = (int)lnum[ic] - e;
+          const float* p = n >= 4 ? lptr[ic] + e : reinterpret_cast<const float*>(tiles);
+          const v4fu t = *(const gv4fu*)p;
+          v[q] = make_float4(t.x, t.y, t.z, t.w);
+          if (i < nl) {
+            vm |= ((1u << max(0, min(4, n))) - 1u) << (4 * q);
+            part |= n > 0 && n < 4;
+          }
         }
-      }
-      {
-        // band slots: one atomic per wavefront, shared out by a wave scan
-        const uint32_t bc = (uint32_t)__popc(bm);
-        const uint32_t incl = wave_incl_scan(bc);
-        const uint32_t wtot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-        uint32_t wbase = 0u;
-        if ((tid & 63) == 63 && wtot) wbase = atomicAdd(&nband, wtot);
-        wbase = (uint32_t)__builtin_amdgcn_readlane((int)wbase, 63);
-        uint32_t slot = wbase + incl - bc;
+        if (__any(part)) {
 #pragma unroll 1
-        for (uint32_t m2 = bm; m2; m2 &= m2 - 1u, ++slot) {
-          const uint32_t key = mag_key(pick_elem(v, __ffs(m2) - 1));
-          atomicAdd(&h[(key >> kH2Shift) & (kH2Bins - 1)], 1u);
-          if (slot < (uint32_t)kBandCap) bandk[slot] = key;
-          else if (slot < rcap) rbtmp[(size_t)w * rcap + slot] = key;
+          for (int q = 0; q < kSteps; ++q) {
+            const uint32_t have = vm >> (4 * q) & 15u;
+            if (have == 0u || have == 15u) continue;
+            const gfloat* g = gptr(lptr[line_of(b0, q)]) + e;
+            const float x0 = g[0], x1 = have & 2u ? g[1] : 0.f, x2 = have & 4u ? g[2] : 0.f;
+#pragma unroll
+            for (int c = 0; c < kSteps; ++c)
+              if (c == q) v[c] = make_float4(x0, x1, x2, 0.f);
+          }
         }
-      }
-      uint32_t tot;
-      const uint32_t ex = block_scan<NT>((uint32_t)__popc(hm), wsum, &tot);
-      if (cw + tot > rcap) fits = false;
-      if (fits && hm) {
-        uint4* __restrict__ dst = cdst + cw + ex;
+      };
+      fetch(0);
 #pragma unroll 1
-        for (uint32_t m2 = hm; m2; m2 &= m2 - 1u, ++dst) {
-          const int j = __ffs(m2) - 1;
-          const uint64_t a = reinterpret_cast<uint64_t>(rp + j);
-          *dst = make_uint4(gidx0 + (uint32_t)j, __float_as_uint(pick_elem(v, j)), (uint32_t)a,
-                            (uint32_t)(a >> 32));
+      for (uint32_t b0 = 0; b0 < nl; b0 += kPerRound) {
+        // candidates: bit 4 q + j of hm is element e + j of step q's line (the
+        // sign of lo - 1 - key, both below 2^31, shifted in from the top)
+        uint32_t hm = 0u;
+#pragma unroll
+        for (int q = kSteps - 1; q >= 0; --q) {
+          const float x[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+#pragma unroll
+          for (int j = 3; j >= 0; --j)
+            hm = __builtin_amdgcn_alignbit(hm, lo - 1u - mag_key(x[j]), 31);
         }
+        hm &= vm;  // (vm has no bit above the last step's)
+        // places: steps, then lanes, within the wavefront (two steps' counts to a
+        // word)
+        uint32_t at[kSteps], wtot = 0u;
+#pragma unroll
+        for (int q = 0; q < kSteps; q += 2) {
+          const uint32_t pk = (uint32_t)__popc((hm >> (4 * q)) & 15u) |
+                              (uint32_t)__popc((hm >> (4 * q + 4)) & 15u) << 16;
+          const uint32_t in = wave_incl_scan(pk);
+          const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)in, 63);
+          at[q] = wtot + ((in - pk) & 0xFFFFu);
+          wtot += all & 0xFFFFu;
+          at[q + 1] = wtot + ((in - pk) >> 16);
+          wtot += all >> 16;
+        }
+        if (lane == 0) wsum[tid >> 6] = wtot;
+        __syncthreads();
+        uint32_t tot = 0u, ex = 0u;
+#pragma unroll
+        for (int i = 0; i < NT / 64; ++i) {
+          const uint32_t sv = wsum[i];
+          ex += i < (tid >> 6) ? sv : 0u;
+          tot += sv;
+        }
+        if (cw + tot > rcap) fits = false;
+#pragma unroll
+        for (int q = 0; q < kSteps; ++q) {
+          uint32_t r = ex + at[q];
+          const uint32_t code = line_of(b0, q) * kLine + e;
+#pragma unroll 1
+          for (uint32_t m2 = (hm >> (4 * q)) & 15u; m2; m2 &= m2 - 1u, ++r)
+            lcode[r] = (uint16_t)(code + (uint32_t)(__ffs(m2) - 1));
+        }
+        __syncthreads();
+        // one candidate per thread (whole wavefronts), read again from the L2;
+        // the next round's lines are requested behind the first of them
+        uint4* __restrict__ dst = cdst + cw;
+        uint32_t c = tid, li = 0u, j = 0u;
+        float x = 0.0f;
+        auto take = [&]() {
+          const uint32_t code = lcode[min(c, tot - 1u)];
+          li = code / kLine;
+          j = code % kLine;
+          x = *gptr(lptr[li] + j);
+        };
+        if ((c & ~63u) < tot) take();
+        fetch(b0 + kPerRound);
+#pragma unroll 1
+        while ((c & ~63u) < tot) {
+          const bool have = c < tot;
+          const uint32_t key = mag_key(x);
+          if (have && fits) {
+            const uint64_t a = reinterpret_cast<uint64_t>(lptr[li] + j);
+            dst[c] = make_uint4(lgidx[li] + j, __float_as_uint(x), (uint32_t)a,
+                                (uint32_t)(a >> 32));
+          }
+          // band slots: one atomic per wavefront
+          const bool band = have && (key >> kH1Shift) == B1;
+          const uint64_t bal = __ballot(band);
+          if (bal) {
+            uint32_t base = 0u;
+            if (lane == 0) base = atomicAdd(&nband, (uint32_t)__popcll(bal));
+            base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+            if (band) {
+              const uint32_t slot = base + __builtin_amdgcn_mbcnt_hi(
+                  (uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+              atomicAdd(&h[(key >> kH2Shift) & (kH2Bins - 1)], 1u);
+              if (slot < (uint32_t)kBandCap) bandk[slot] = key;
+              else if (slot < rcap) rbtmp[(size_t)w * rcap + slot] = key;
+            }
+          }
+          c += NT;
+          if ((c & ~63u) < tot) take();
+        }
+        cw += tot;
       }
-      cw += tot;
+      __syncthreads();  // the lists are refilled
     }
-    // the line list is refilled for the next chunk (skipped after the last)
-    if (c0 + (uint32_t)kFlCap < F) __syncthreads();
   }
 
   // band members by level-2 bin from the top (thread t owns the kB2 bins
@@ -1005,15 +1103,11 @@ __device__ __forceinline__ void for_class2(int wlim, uint32_t B2, uint32_t rcap,
   }
 }
 
-// (Four waves per SIMD: two 512-thread workgroups, or one of 1,024 threads,
-// per compute unit, so that up to 512 regions are all resident at once; at
-// 129 registers the 512-thread shape fitted one per compute unit and a
-// grid of 424 regions ran in two rounds.)
 template <int NT>
 __global__ __launch_bounds__(NT, 4) void k_finish(
     const TileDesc* __restrict__ tiles, const GroupDesc* __restrict__ groups,
     const GroupState* __restrict__ st, const uint16_t* __restrict__ summ, int64_t nlines,
-    int lpt, uint32_t rcap, const uint32_t* __restrict__ hist2,
+    int lpt, int32_t rl, uint32_t rcap, const uint32_t* __restrict__ hist2,
     const uint32_t* __restrict__ rbin, const uint4* __restrict__ rcand,
     const uint32_t* __restrict__ rband,
     const uint32_t* __restrict__ rsuf, const uint2* __restrict__ rcnt,
@@ -1030,8 +1124,7 @@ __global__ __launch_bounds__(NT, 4) void k_finish(
   __shared__ uint16_t c2reg[kC2Cap];     // ... and their regions
   __shared__ uint32_t n2;
   __shared__ uint32_t any_unstored, last;
-  constexpr int kRegPerThread = kSMaxGroups / NT;
-  const int tid = threadIdx.x, w = blockIdx.x, G = gridDim.x;
+  const int tid = threadIdx.x, w = blockIdx.x, G = gridDim.x;  // (G <= kFMaxGroups <= NT)
   for (int i = tid; i < kH3Bins; i += NT) h[i] = 0u;
   for (int i = tid; i < kOvWords; i += NT) {
     ovbits[i] = 0u;
@@ -1063,13 +1156,7 @@ __global__ __launch_bounds__(NT, 4) void k_finish(
   }
   const uint4 v0 = (cb < ce || rounds) ? mc[rounds ? (uint32_t)tid : cb]
                                        : make_uint4(0u, 0u, 0u, 0u);
-  uint2 cr[kRegPerThread];
-#pragma unroll
-  for (int q = 0; q < kRegPerThread; ++q) {
-    const int r = q * NT + tid;
-    cr[q] = make_uint2(0u, 0u);
-    if (q * NT < G && r < G) cr[q] = rcnt[r];
-  }
+  const uint2 cr = tid < G ? rcnt[tid] : make_uint2(0u, 0u);
 
   // level 2 (the pick's barriers also publish the cleared LDS above)
   block_pick<NT, kH2Bins, 1>(hist2, s0.need, wsum, res);
@@ -1083,43 +1170,38 @@ __global__ __launch_bounds__(NT, 4) void k_finish(
   // rbin. gtb: this thread's share of the elements above T before region w.
   uint32_t gtb = 0u;
   bool slow = false;  // some region has more than kPerBin class-2 members
-#pragma unroll
-  for (int q = 0; q < kRegPerThread; ++q) {
-    if (q * NT >= G) break;
-    const int r = q * NT + tid;
-    if (r >= G) continue;
-    const uint32_t bw = cr[q].y & 0x7FFFFFFFu;
-    const bool ov = (cr[q].y >> 31) != 0u;
+  if (tid < G) {
+    const int r = tid;
+    const uint32_t bw = cr.y & 0x7FFFFFFFu;
+    const bool ov = (cr.y >> 31) != 0u;
     if (ov) {
       atomicOr(&ovbits[r >> 5], 1u << (r & 31));
       any_unstored = 1u;
     }
     if (!bw) {
-      if (r < w) gtb += cr[q].x & 0x7FFFFFFFu;
-      continue;
-    }
-    const uint32_t* sr = rsuf + (size_t)r * kH2Bins;
-    const uint32_t above = sr[B2];
-    const uint32_t at = (B2 ? sr[B2 - 1] : bw) - above;
-    const uint4 e = *reinterpret_cast<const uint4*>(rbin + ((size_t)B2 * G + r) * kPerBin);
-    if (r < w) gtb += (cr[q].x & 0x7FFFFFFFu) - bw + above;
-    if (ov) {
-      if (at) atomicOr(&c2bits[r >> 5], 1u << (r & 31));  // its lines are walked below
-      continue;
-    }
-    if (at > (uint32_t)kPerBin) {
-      slow = true;
-      continue;
-    }
-    const uint32_t ek[4] = {e.x, e.y, e.z, e.w};
+      if (r < w) gtb += cr.x & 0x7FFFFFFFu;
+    } else {
+      const uint32_t* sr = rsuf + (size_t)r * kH2Bins;
+      const uint32_t above = sr[B2];
+      const uint32_t at = (B2 ? sr[B2 - 1] : bw) - above;
+      const uint4 e = *reinterpret_cast<const uint4*>(rbin + ((size_t)B2 * G + r) * kPerBin);
+      if (r < w) gtb += (cr.x & 0x7FFFFFFFu) - bw + above;
+      if (ov) {
+        if (at) atomicOr(&c2bits[r >> 5], 1u << (r & 31));  // its lines are walked below
+      } else if (at > (uint32_t)kPerBin) {
+        slow = true;
+      } else {
+        const uint32_t ek[4] = {e.x, e.y, e.z, e.w};
 #pragma unroll
-    for (int c = 0; c < kPerBin; ++c) {
-      if ((uint32_t)c < at) {
-        atomicAdd(&h[ek[c] & (kH3Bins - 1)], 1u);
-        const uint32_t slot = atomicAdd(&n2, 1u);
-        if (slot < (uint32_t)kC2Cap) {
-          c2key[slot] = ek[c];
-          c2reg[slot] = (uint16_t)r;
+        for (int c = 0; c < kPerBin; ++c) {
+          if ((uint32_t)c < at) {
+            atomicAdd(&h[ek[c] & (kH3Bins - 1)], 1u);
+            const uint32_t slot = atomicAdd(&n2, 1u);
+            if (slot < (uint32_t)kC2Cap) {
+              c2key[slot] = ek[c];
+              c2reg[slot] = (uint16_t)r;
+            }
+          }
         }
       }
     }
@@ -1179,10 +1261,14 @@ __global__ __launch_bounds__(NT, 4) void k_finish(
         const int r = wi * 32 + __ffs(m) - 1;
         m &= m - 1u;
         if (r >= wlim) break;
-        LineSpan lr;
-        lr.load(tiles, summ, nlines, ((int64_t)r * NT + tid) * lpt, lpt);
-        walk_mask(lr, lr.flagged([&](int) -> uint32_t { return thr2; }), in_cls2,
-                  [&](int, const TileDesc&, int, float, uint32_t key) { f(key); });
+#pragma unroll 1
+        for (int32_t s0 = 0; s0 < rl; s0 += NT * lpt) {
+          LineSpan lr;
+          lr.load(tiles, summ, min(nlines, (int64_t)(r + 1) * rl),
+                  (int64_t)r * rl + s0 + tid * lpt, lpt);
+          walk_mask(lr, lr.flagged([&](int) -> uint32_t { return thr2; }), in_cls2,
+                    [&](int, const TileDesc&, int, float, uint32_t key) { f(key); });
+        }
       }
     }
   };
@@ -1206,28 +1292,16 @@ __global__ __launch_bounds__(NT, 4) void k_finish(
   }
   lines_class2(w, tally);
 
-  // this region: its stored candidate (at most one per thread), or its
-  // lines. Counts of (key > T) and (key == T) in position order (the rounds
-  // count theirs as they go).
-  LineSpan ls;
-  uint32_t mask = 0u;
-  if (own_ov) {
-    ls.load(tiles, summ, nlines, ((int64_t)w * NT + tid) * lpt, lpt);
-    mask = ls.flagged([&](int) -> uint32_t { return T; });
-  }
-  auto at_least_T = [&](int, uint32_t key) -> bool { return key >= T; };
+  // this region's stored candidate (at most one per thread): counts of (key >
+  // T) and (key == T) in position order (the rounds, and a region without
+  // stored candidates, count theirs as they go)
   uint32_t gt = 0u, eq = 0u;
   auto count = [&](float x) {
     const uint32_t key = mag_key(x);
     gt += (key > T) ? 1u : 0u;
     eq += (key == T) ? 1u : 0u;
   };
-  if (own_ov) {
-    walk_mask(ls, mask, at_least_T,
-              [&](int, const TileDesc&, int, float x, uint32_t) { count(x); });
-  } else if (cb < ce) {
-    count(__uint_as_float(v0.y));  // (fetched at the start)
-  }
+  if (cb < ce) count(__uint_as_float(v0.y));  // (fetched at the start)
   const uint32_t sv[4] = {gt, eq, gtb, eqb};
   uint32_t pre[4], tot[4];
   block_scan4<NT>(sv, wsum, pre, tot);
@@ -1240,12 +1314,8 @@ __global__ __launch_bounds__(NT, 4) void k_finish(
   // stored (their level-2 class members, above), so such a region does not
   // zero its residuals here: it records its range of output slots, and the
   // last workgroup to finish zeroes the residuals at those slots' indices.
+  // (Such a region stored no candidates either, which include its band.)
   const bool defer = (mine.y >> 31) != 0u;
-  if (defer && tid == 0) {
-    const uint32_t lo = tot[2] + min(tot[3], need3);
-    const uint32_t hi = tot[2] + tot[0] + min(tot[3] + tot[1], need3);
-    rzr[w] = (uint64_t)min(lo, k) | ((uint64_t)min(hi, k) << 32);
-  }
   uint32_t gtr = tot[2] + pre[0];
   uint32_t eqr = tot[3] + pre[1];
   // write
@@ -1295,13 +1365,35 @@ __global__ __launch_bounds__(NT, 4) void k_finish(
       eqr_r += rt >> 16;
       cur = nxt;
     }
-  } else if (gt + eq == 0u) {
-    // nothing to write
   } else if (own_ov) {
-    walk_mask(ls, mask, at_least_T, [&](int, const TileDesc& t, int e, float x, uint32_t) {
-      write((uint32_t)(t.gstart + e), t.r + e, x);
-    });
-  } else if (cb < ce) {
+    // from its lines, block by block: counts, then places
+    uint32_t gtr_r = tot[2], eqr_r = tot[3];
+    const uint32_t first = gtr_r + min(eqr_r, need3);
+    auto at_least_T = [&](int, uint32_t key) -> bool { return key >= T; };
+#pragma unroll 1
+    for (int32_t s0 = 0; s0 < rl; s0 += NT * lpt) {
+      LineSpan ls;
+      ls.load(tiles, summ, min(nlines, (int64_t)(w + 1) * rl), (int64_t)w * rl + s0 + tid * lpt,
+              lpt);
+      const uint32_t mask = ls.flagged([&](int) -> uint32_t { return T; });
+      gt = eq = 0u;
+      walk_mask(ls, mask, at_least_T,
+                [&](int, const TileDesc&, int, float x, uint32_t) { count(x); });
+      uint2 bt;
+      const uint2 bp = block_scan2<NT>(gt, eq, wsum, &bt);
+      gtr = gtr_r + bp.x;
+      eqr = eqr_r + bp.y;
+      if (gt + eq)
+        walk_mask(ls, mask, at_least_T, [&](int, const TileDesc& t, int e, float x, uint32_t) {
+          write((uint32_t)(t.gstart + e), t.r + e, x);
+        });
+      gtr_r += bt.x;
+      eqr_r += bt.y;
+    }
+    if (defer && tid == 0)
+      rzr[w] = (uint64_t)min(first, k) |
+               ((uint64_t)min(gtr_r + min(eqr_r, need3), k) << 32);
+  } else if (gt + eq) {
     write(v0.x, reinterpret_cast<float*>(((uint64_t)v0.w << 32) | v0.z), __uint_as_float(v0.y));
   }
   if (!any_unstored) return;  // (uniform) the common case ends here
@@ -3171,37 +3263,38 @@ hipError_t launch_pick(int level, const GroupDesc* groups, GroupState* st,
 
 hipError_t launch_collect(const TileDesc* tiles, const GroupDesc* groups, GroupState* st,
                           const uint32_t* hist1, int nslots, const uint16_t* summ, int64_t nlines,
-                          int lpt, int32_t grid, int32_t block, uint32_t rcap, uint32_t* hist2, uint32_t* rbin,
-                          uint32_t* rcand, uint32_t* rband, uint32_t* rbtmp, uint32_t* rsuf,
+                          int lpt, int32_t rl, int32_t grid, int32_t block, uint32_t rcap,
+                          uint32_t* hist2, uint32_t* rbin, uint32_t* rcand, uint32_t* rband, uint32_t* rbtmp, uint32_t* rsuf,
                           uint32_t* rcnt, hipStream_t s, const Ev& ev) {
-  if (nslots != kSlotsOne) return hipErrorInvalidValue;
+  if (nslots != kSlotsOne || grid > kFMaxGroups) return hipErrorInvalidValue;
   if (block == kCBlockSmall)
     return launch(k_collect<kCBlockSmall>, dim3(grid), dim3(block), s, ev, tiles, groups, st,
                   hist1, summ, hist2, rbin, reinterpret_cast<uint4*>(rcand), rband, rbtmp, rsuf,
-                  reinterpret_cast<uint2*>(rcnt), rcap, lpt, nlines);
+                  reinterpret_cast<uint2*>(rcnt), rcap, lpt, rl, nlines);
   if (block == kSBlock)
     return launch(k_collect<kSBlock>, dim3(grid), dim3(block), s, ev, tiles, groups, st, hist1,
                   summ, hist2, rbin, reinterpret_cast<uint4*>(rcand), rband, rbtmp, rsuf,
-                  reinterpret_cast<uint2*>(rcnt), rcap, lpt, nlines);
+                  reinterpret_cast<uint2*>(rcnt), rcap, lpt, rl, nlines);
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_finish(const TileDesc* tiles, const GroupDesc* groups,
                          const GroupState* st, const uint16_t* summ, int64_t nlines, int lpt,
-                         int32_t grid, int32_t block, uint32_t rcap, const uint32_t* hist2, const uint32_t* rbin,
-                         const uint32_t* rcand, const uint32_t* rband, const uint32_t* rsuf,
+                         int32_t rl, int32_t grid, int32_t block, uint32_t rcap,
+                         const uint32_t* hist2, const uint32_t* rbin, const uint32_t* rcand, const uint32_t* rband, const uint32_t* rsuf,
                          const uint32_t* rcnt, int32_t* idx_out, void* val_out, int val16,
                          uint32_t* clear_next, int64_t clear_words, uint32_t* ticket,
                          uint32_t* rzr, hipStream_t s, const Ev& ev) {
   uint64_t* rz = reinterpret_cast<uint64_t*>(rzr);
+  if (grid > kFMaxGroups) return hipErrorInvalidValue;
   if (block == kCBlockSmall)
     return launch(k_finish<kCBlockSmall>, dim3(grid), dim3(block), s, ev, tiles, groups, st, summ,
-                  nlines, lpt, rcap, hist2, rbin, reinterpret_cast<const uint4*>(rcand), rband,
+                  nlines, lpt, rl, rcap, hist2, rbin, reinterpret_cast<const uint4*>(rcand), rband,
                   rsuf, reinterpret_cast<const uint2*>(rcnt), idx_out, val_out, val16,
                   clear_next, clear_words, ticket, rz);
   if (block == kSBlock)
     return launch(k_finish<kSBlock>, dim3(grid), dim3(block), s, ev, tiles, groups, st, summ,
-                  nlines, lpt, rcap, hist2, rbin, reinterpret_cast<const uint4*>(rcand), rband,
+                  nlines, lpt, rl, rcap, hist2, rbin, reinterpret_cast<const uint4*>(rcand), rband,
                   rsuf, reinterpret_cast<const uint2*>(rcnt), idx_out, val_out, val16,
                   clear_next, clear_words, ticket, rz);
   return hipErrorInvalidValue;
@@ -3285,11 +3378,9 @@ hipError_t launch_ms_emit(const TileDesc* tiles, const uint16_t* summ, int64_t n
 
 int32_t select_max_groups() { return kSMaxGroups; }
 int32_t select_block() { return kSBlock; }
-int32_t collect_block(int64_t nlines, int64_t k, int64_t d) {
-  const bool fits = nlines <= (int64_t)kCBlockSmall * kSMaxLpt * kCDenseMaxGroups;
-  return (nlines <= kCSmallLines || (k * kCDenseDiv >= d && fits)) ? kCBlockSmall : kSBlock;
-}
+int32_t collect_block(int64_t nlines) { return nlines <= kCSmallLines ? kCBlockSmall : kSBlock; }
 int32_t select_max_lpt() { return kSMaxLpt; }
+int32_t collect_regions() { return kFMaxGroups; }
 int32_t emit_lds_groups() { return kEmitLdsGroups; }
 
 hipError_t launch_seg(const int32_t* idx, int64_t stride, const int32_t* nnz, int32_t P,

@@ -93,3 +93,53 @@ def test_sparsify_off_grid(gs, rs, mode):
         assert (got[:rs] == guard).all() and (got[rs + n:] == guard).all()
         back = gb[t].cpu().numpy()
         assert_bitwise(back[gs:gs + n], grads[t], f"gradient[{t}]")
+
+
+# One exact selection over regions of several blocks of lines (more than 2^27
+# elements), each holding more members of the threshold's bin than it can store:
+# the finish reads the lines, in every workgroup. x is +-1 with 1,000 larger
+# elements, so the selection is those and the first positions of the rest.
+def test_sparsify_regions_of_blocks_over_capacity():
+    import torch
+    dev = need_gpu()
+    d, big, k = (1 << 27) + 4097, 1000, 5000
+    announce(f"sparsify regions of blocks, ties everywhere, d={d}")
+    gen_ = torch.Generator(device=dev).manual_seed(7)
+    g = torch.randint(0, 2, (d,), generator=gen_, device=dev).float() * 2 - 1
+    where = torch.randperm(d - 1, generator=gen_, device=dev)[:big] + 1
+    g[where] *= 1.5
+    r = torch.zeros(d, device=dev)
+    status = torch.zeros(1, dtype=torch.int32, device=dev)
+    idx, val = tk.SparsifyPlan([d], k=k).bind([g], [r]).execute(status=status)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    keep = g.abs() > 1
+    rest = (~keep).nonzero()[:k - big, 0]
+    keep[rest] = True
+    want = keep.nonzero()[:, 0]
+    assert torch.equal(idx.long(), want)
+    assert torch.equal(val, g[want])
+    g[want] = 0.0
+    assert torch.equal(r, g)
+
+
+# Region splits: as many regions as there can be, a last one of a few lines, one
+# region, a tensor list whose tiles are mostly empty.
+@pytest.mark.parametrize("sizes,rho", [([256 * 2048 * 32], 0.001), ([256 * 2048 * 32 + 33], 0.01),
+                                       ([2049 * 32 * 4 + 5], 0.02), ([5], 0.3),
+                                       ([37] * 700 + [50_000], 0.05)])
+def test_sparsify_region_splits(sizes, rho):
+    import torch
+    dev = need_gpu()
+    announce(f"sparsify region splits {sizes[:3]} x {len(sizes)}")
+    rng = np.random.default_rng(len(sizes))
+    grads = [rng.standard_normal(n).astype(np.float32) for n in sizes]
+    grads[0][:] = np.round(grads[0], 2)  # (ties)
+    res = [np.zeros(n, np.float32) for n in sizes]
+    g, r = to_dev(grads, dev), to_dev(res, dev)
+    idx, val = tk.SparsifyPlan(sizes, rho=rho, check=True).bind(g, r).execute()
+    torch.cuda.synchronize()
+    oi, ov, orr, _ = orc().sparsify(grads, res, rho=rho, mode=oracle.GLOBAL)
+    assert_bitwise(idx.cpu().numpy(), oi, "idx")
+    assert_bitwise(val.cpu().numpy(), ov, "val")
+    assert_bitwise(gen.concat(to_host(r)), np.concatenate([np.ravel(a) for a in orr]), "residual")
