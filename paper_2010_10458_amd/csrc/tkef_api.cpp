@@ -778,6 +778,7 @@ struct tkef_update_plan_s {
   std::vector<UpdTensor> tens;
   std::vector<int32_t> tile_first;
   std::vector<int32_t> tpair;  // LARS: first (tile, tensor) pair of each tensor; [T] = pairs
+  std::vector<char> tables;    // the workspace's start, as bind writes it
   size_t off_tens = 0, off_first = 0, off_seg = 0, off_tpair = 0, off_part = 0, off_rate = 0,
          off_gptr = 0, off_lists = 0, ws_bytes = 0;
   bool table = false;  // lists given as per-worker pointers (WorkerList table in ws)
@@ -836,17 +837,19 @@ int update_plan_create(const int64_t* numels, int32_t ntensors, int32_t P, int64
     }
     p->tens.resize(ntensors);
     size_t o = 0;
+    // the tables that the host writes come first, next to each other: one copy
+    p->table = table;
     p->off_tens = o;   o = align_up(o + p->tens.size() * sizeof(UpdTensor));
     p->off_first = o;  o = align_up(o + p->tile_first.size() * sizeof(int32_t));
-    p->off_seg = o;    o = align_up(o + (size_t)P * (p->ntiles_u + 1) * sizeof(int32_t));
     p->off_tpair = o;  o = align_up(o + p->tpair.size() * sizeof(int32_t));
-    p->off_part = o;   o = align_up(o + (size_t)p->tpair[ntensors] * 16);
-    p->off_rate = o;   o = align_up(o + (size_t)ntensors * sizeof(double));
-    p->off_gptr = o;   o = align_up(o + (size_t)ntensors * sizeof(float*));
-    p->table = table;
     if (table) {
       p->off_lists = o;  o = align_up(o + (size_t)P * sizeof(WorkerList));
     }
+    p->tables.resize(o);
+    p->off_seg = o;    o = align_up(o + (size_t)P * (p->ntiles_u + 1) * sizeof(int32_t));
+    p->off_part = o;   o = align_up(o + (size_t)p->tpair[ntensors] * 16);
+    p->off_rate = o;   o = align_up(o + (size_t)ntensors * sizeof(double));
+    p->off_gptr = o;   o = align_up(o + (size_t)ntensors * sizeof(float*));
     p->ws_bytes = o;
   } catch (const std::bad_alloc&) {
     delete p;
@@ -909,17 +912,14 @@ extern "C" int tkef_update_plan_bind(tkef_update_plan plan, float* const* params
     plan->tens[t].goff = plan->goff[t];
     plan->tens[t].n = plan->numels[t];
   }
-  char* base = static_cast<char*>(ws);
-  hipError_t e = hipMemcpyAsync(base + plan->off_tens, plan->tens.data(),
-                                plan->tens.size() * sizeof(UpdTensor), hipMemcpyHostToDevice,
-                                stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(base + plan->off_first, plan->tile_first.data(),
-                       plan->tile_first.size() * sizeof(int32_t), hipMemcpyHostToDevice,
-                       stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(base + plan->off_tpair, plan->tpair.data(),
-                       plan->tpair.size() * sizeof(int32_t), hipMemcpyHostToDevice, stream);
+  // One copy for all tables (a pageable copy costs the host several
+  // microseconds whatever its size; the one-shot calls bind every time)
+  char* tab = plan->tables.data();
+  std::memcpy(tab + plan->off_tens, plan->tens.data(), plan->tens.size() * sizeof(UpdTensor));
+  std::memcpy(tab + plan->off_first, plan->tile_first.data(),
+              plan->tile_first.size() * sizeof(int32_t));
+  std::memcpy(tab + plan->off_tpair, plan->tpair.data(), plan->tpair.size() * sizeof(int32_t));
+  hipError_t e = hipMemcpyAsync(ws, tab, plan->tables.size(), hipMemcpyHostToDevice, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e != hipSuccess) {
     plan->bound_ws = nullptr;
@@ -1172,13 +1172,9 @@ extern "C" int tkef_aggregate_update(float* const* params, float* const* momentu
     tkef_update_plan_destroy(p);
     return rc;
   }
-  // the worker table goes in first; bind's synchronization covers its copy
+  // bind copies the worker table with the others
   char* base = static_cast<char*>(ws);
-  if (hipMemcpyAsync(base + p->off_lists, lists.data(), lists.size() * sizeof(WorkerList),
-                     hipMemcpyHostToDevice, stream) != hipSuccess) {
-    tkef_update_plan_destroy(p);
-    return TKEF_EHIP;
-  }
+  std::memcpy(p->tables.data() + p->off_lists, lists.data(), lists.size() * sizeof(WorkerList));
   rc = tkef_update_plan_bind(p, params, momentum, ws, ws_bytes, stream);
   if (!rc) {
     const UpdTensor* tens = reinterpret_cast<const UpdTensor*>(base + p->off_tens);
