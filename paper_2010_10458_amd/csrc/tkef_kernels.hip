@@ -1758,56 +1758,75 @@ typedef __attribute__((address_space(1))) const int32_t gint;
 // update tile u or later; seg[ntiles_u * P + p] = nnz_p. Tile-major, so the
 // workgroup of tile u reads two contiguous rows. Also flags unsorted or
 // out-of-range lists in the status word.
+// Bound by its scattered 4-byte stores (one per worker and tile: an empty list
+// costs as much, and non-temporal or write-through stores 32 and 14 us). Two
+// entries per thread: P = 128 lists of 25,600 entries over 6,240 tiles 10.2 ->
+// 9.5 us; four 10.8, eight 11.1, two in 512-thread workgroups 10.4.
+constexpr int kSegPer = 2;  // list entries per thread
 template <bool kTable>
-__global__ void k_seg(ListsArg lists, int32_t P, int32_t d, int32_t ntiles_u,
-                      int32_t* __restrict__ seg, uint32_t* __restrict__ status) {
+__global__ __launch_bounds__(256) void k_seg(ListsArg lists, int32_t P, int32_t d,
+                                             int32_t ntiles_u, int32_t* __restrict__ seg,
+                                             uint32_t* __restrict__ status) {
   const int p = blockIdx.y;
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int32_t i_here = 0, i_prev = 0;
+  const int64_t j0 = (int64_t)blockIdx.x * (256 * kSegPer) + threadIdx.x;
+  // this thread's entries j0 + 256 q and the ones before them, all requested
+  // together. The gathered form reads them before the count is known: every
+  // j < stride is inside the list's storage (none for stride == 0, a
+  // kernel-wide value).
+  int32_t here[kSegPer], prev[kSegPer];
   int64_t n;
   if constexpr (kTable) {
     const WorkerList wl = lists.table[p];
     n = wl.n;
-    if (j < n) {
-      const gint* L = (const gint*)wl.idx;
-      i_here = L[j];
-      i_prev = L[j > 0 ? j - 1 : 0];
+    const gint* L = (const gint*)wl.idx;
+    if (n > 0) {
+#pragma unroll
+      for (int q = 0; q < kSegPer; ++q) {
+        const int64_t j = min(j0 + 256 * q, n - 1);
+        here[q] = L[j];
+        prev[q] = L[j > 0 ? j - 1 : 0];
+      }
     }
   } else {
-    // this entry and the one before it, read before the count is known
-    // (every j < stride is inside the list's storage), so all three loads
-    // overlap; no storage at all for stride == 0 (a kernel-wide value)
     const int64_t stride = lists.stride;
     const int32_t* __restrict__ L = lists.idx + (int64_t)p * stride;
-    const int64_t jc = j < stride ? j : stride - 1;
     if (stride > 0) {
-      i_here = L[jc];
-      i_prev = L[jc > 0 ? jc - 1 : 0];
+#pragma unroll
+      for (int q = 0; q < kSegPer; ++q) {
+        const int64_t j = min(j0 + 256 * q, stride - 1);
+        here[q] = L[j];
+        prev[q] = L[j > 0 ? j - 1 : 0];
+      }
     }
     n = lists.nnz ? (int64_t)lists.nnz[p] : stride;
     n = n < 0 ? 0 : (n > stride ? stride : n);
   }
   if (n == 0) {
-    for (int64_t u = j; u <= ntiles_u; u += (int64_t)gridDim.x * blockDim.x)
+    for (int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x; u <= ntiles_u;
+         u += (int64_t)gridDim.x * 256)
       seg[u * P + p] = 0;
     return;
   }
-  if (j >= n) return;
   auto tile_of = [&](int32_t i) -> int32_t {
     return i < 0 ? 0 : (i >= d ? ntiles_u - 1 : (i >> kUShift));
   };
-  const int32_t i = i_here;
-  uint32_t bad = (i < 0 || i >= d) ? TKEF_STATUS_INDEX_RANGE : 0u;
-  const int32_t t = tile_of(i);
-  int32_t tp = -1;
-  if (j > 0) {
-    const int32_t ip = i_prev;
-    if (ip > i) bad |= TKEF_STATUS_UNSORTED;
-    tp = tile_of(ip);
+  uint32_t bad = 0u;
+#pragma unroll
+  for (int q = 0; q < kSegPer; ++q) {
+    const int64_t j = j0 + 256 * q;
+    if (j >= n) break;
+    const int32_t i = here[q];
+    if (i < 0 || i >= d) bad |= TKEF_STATUS_INDEX_RANGE;
+    const int32_t t = tile_of(i);
+    int32_t tp = -1;
+    if (j > 0) {
+      if (prev[q] > i) bad |= TKEF_STATUS_UNSORTED;
+      tp = tile_of(prev[q]);
+    }
+    for (int32_t u = tp + 1; u <= t; ++u) seg[(int64_t)u * P + p] = (int32_t)j;
+    if (j == n - 1)
+      for (int32_t u = t + 1; u <= ntiles_u; ++u) seg[(int64_t)u * P + p] = (int32_t)n;
   }
-  for (int32_t u = tp + 1; u <= t; ++u) seg[(int64_t)u * P + p] = (int32_t)j;
-  if (j == n - 1)
-    for (int32_t u = t + 1; u <= ntiles_u; ++u) seg[(int64_t)u * P + p] = (int32_t)n;
   if (bad && status) atomicOr(status, bad);
 }
 
@@ -3386,7 +3405,7 @@ int32_t emit_lds_groups() { return kEmitLdsGroups; }
 hipError_t launch_seg(const int32_t* idx, int64_t stride, const int32_t* nnz, int32_t P,
                       int32_t d, int32_t ntiles_u, int32_t* seg, uint32_t* status,
                       hipStream_t s, const Ev& ev) {
-  int64_t bx = (stride + 255) / 256;
+  int64_t bx = (stride + 256 * kSegPer - 1) / (256 * kSegPer);
   if (bx < 1) bx = 1;
   const ListsArg lists{idx, nullptr, stride, nnz, nullptr};
   return launch(k_seg<false>, dim3((unsigned)bx, (unsigned)P), dim3(256), s, ev, lists, P, d,
@@ -3396,7 +3415,7 @@ hipError_t launch_seg(const int32_t* idx, int64_t stride, const int32_t* nnz, in
 hipError_t launch_seg_table(const WorkerList* table, int32_t P, int64_t max_n, int32_t d,
                             int32_t ntiles_u, int32_t* seg, uint32_t* status, hipStream_t s,
                             const Ev& ev) {
-  int64_t bx = (max_n + 255) / 256;
+  int64_t bx = (max_n + 256 * kSegPer - 1) / (256 * kSegPer);
   if (bx < 1) bx = 1;
   const ListsArg lists{nullptr, nullptr, 0, nullptr, table};
   return launch(k_seg<true>, dim3((unsigned)bx, (unsigned)P), dim3(256), s, ev, lists, P, d,

@@ -143,3 +143,35 @@ def test_sparsify_region_splits(sizes, rho):
     assert_bitwise(idx.cpu().numpy(), oi, "idx")
     assert_bitwise(val.cpu().numpy(), ov, "val")
     assert_bitwise(gen.concat(to_host(r)), np.concatenate([np.ravel(a) for a in orr]), "residual")
+
+
+# Segment search: lists that end just at, before and after the entries one
+# workgroup takes (512), empty lists among them, lists over few and many tiles.
+@pytest.mark.parametrize("k", [1, 255, 256, 257, 511, 512, 513, 1025])
+def test_update_list_lengths(k):
+    import torch
+    dev = need_gpu()
+    d, P = 300_007, 5
+    announce(f"update list lengths k={k}")
+    rng = np.random.default_rng(k)
+    idx = np.stack([np.sort(rng.choice(d, size=k, replace=False)) for _ in range(P)]).astype(np.int32)
+    idx[1] = np.sort(rng.choice(4096, size=k, replace=False))     # (one tile)
+    val = rng.integers(-8, 9, (P, k)).astype(np.float32)          # (exact sums)
+    nnz = np.array([k, max(1, k - 1), 0, k // 2, k], np.int32)
+    w0 = np.zeros(d, np.float32)
+    w = torch.zeros(d, device=dev)
+    status = torch.zeros(1, dtype=torch.int32, device=dev)
+    plan = tk.UpdatePlan([d], P=P, stride=k).bind([w])
+    plan.aggregate(torch.from_numpy(idx).to(dev), torch.from_numpy(val).to(dev),
+                   nnz=torch.from_numpy(nnz).to(dev), status=status)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    for p in range(P):
+        np.add.at(w0, idx[p, :nnz[p]], val[p, :nnz[p]])
+    assert_bitwise(w.cpu().numpy(), w0, "sums")
+    # the per-worker form, on the same lists
+    w2 = torch.zeros(d, device=dev)
+    tk.aggregate_update([w2], [(torch.from_numpy(idx[p, :nnz[p]].copy()).to(dev),
+                                torch.from_numpy(val[p, :nnz[p]].copy()).to(dev))
+                               for p in range(P)], lr=-1.0)
+    assert_bitwise(w2.cpu().numpy(), w0, "per-worker lists")
