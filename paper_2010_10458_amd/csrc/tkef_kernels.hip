@@ -21,6 +21,7 @@
 //            are ascending, so tile boundaries are where idx >> shift grows)
 //   update   per tile: LDS accumulation of all workers' entries of the tile,
 //            then one pass applying the SGD step to that parameter range
+#include <algorithm>
 #include <mutex>
 
 #include <hip/hip_ext.h>
@@ -1759,11 +1760,13 @@ typedef __attribute__((address_space(1))) const int32_t gint;
 // workgroup of tile u reads two contiguous rows. Also flags unsorted or
 // out-of-range lists in the status word.
 // Bound by its scattered 4-byte stores (one per worker and tile: an empty list
-// costs as much, and non-temporal or write-through stores 32 and 14 us). Two
-// entries per thread: P = 128 lists of 25,600 entries over 6,240 tiles 10.2 ->
-// 9.5 us; four 10.8, eight 11.1, two in 512-thread workgroups 10.4.
-constexpr int kSegPer = 2;  // list entries per thread
-template <bool kTable>
+// costs as much, and non-temporal or write-through stores 32 and 14 us). With
+// many entries a thread takes kSegPer = 2: P = 128 lists of 25,600 entries over
+// 6,240 tiles 10.2 -> 9.5 us; four 10.8, eight 11.1, two in 512-thread
+// workgroups 10.4. With few (up to kSegFew in all) it takes one: P = 40 lists
+// of 25,600 entries 5.0 us, 5.3 with two.
+constexpr int64_t kSegFew = (int64_t)1 << 21;
+template <bool kTable, int kSegPer>
 __global__ __launch_bounds__(256) void k_seg(ListsArg lists, int32_t P, int32_t d,
                                              int32_t ntiles_u, int32_t* __restrict__ seg,
                                              uint32_t* __restrict__ status) {
@@ -1901,19 +1904,20 @@ constexpr int kPairUnroll = 3;  // list entries per thread and chunk of the accu
 // e, scan the inclusive prefix of the workers' counts in the tile (kUBlock
 // words, the last above every e). A fixed number of steps, the searches side
 // by side, so that their LDS reads overlap.
+template <int U>
 __device__ __forceinline__ void entry_workers(const uint32_t* scan,
-                                              const uint32_t (&e)[kPairUnroll],
-                                              int (&w)[kPairUnroll]) {
+                                              const uint32_t (&e)[U],
+                                              int (&w)[U]) {
 #pragma unroll
-  for (int j = 0; j < kPairUnroll; ++j) w[j] = 0;
+  for (int j = 0; j < U; ++j) w[j] = 0;
 #pragma unroll
   for (int step = kUBlock / 2; step >= 1; step >>= 1) {
-    uint32_t s[kPairUnroll];
+    uint32_t s[U];
 #pragma unroll
-    for (int j = 0; j < kPairUnroll; ++j) s[j] = scan[w[j] + step - 1];
+    for (int j = 0; j < U; ++j) s[j] = scan[w[j] + step - 1];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < kPairUnroll; ++j) w[j] += s[j] <= e[j] ? step : 0;
+    for (int j = 0; j < U; ++j) w[j] += s[j] <= e[j] ? step : 0;
   }
 }
 
@@ -1961,39 +1965,61 @@ struct PairSrc {
 // 73.2 and 46.6 (momentum, norms), two: 73.8 and 46.5. (Two threads
 // walking each worker's own segment, without search or scan: 77.2; several
 // tiles per workgroup with the next tile's entries prefetched: 79-95.)
+//
+// A wavefront without entries does nothing, and a chunk of at most one entry per
+// thread takes that form (P = 5 lists of 3,524 entries, 5.3 M positions: the
+// whole LARS step 34.0 us with one search per entry there is, 35.3 with three
+// per thread always, 33.4 now).
+template <int U, bool kTable>
+__device__ __forceinline__ void load_pairs_of(const PairSrc<kTable>& src, const uint32_t* scan,
+                                              const int32_t* sbeg, int p0, uint32_t q0,
+                                              uint32_t total, int32_t base, int val16,
+                                              int32_t (&li)[kPairUnroll],
+                                              float (&vv)[kPairUnroll]) {
+  uint32_t e[U];
+  int w[U];
+#pragma unroll
+  for (int j = 0; j < U; ++j) e[j] = min(q0 + j * kUBlock + threadIdx.x, total - 1u);
+  entry_workers<U>(scan, e, w);
+  typename PairSrc<kTable>::Ref ref[U];
+#pragma unroll
+  for (int j = 0; j < U; ++j) {
+    const uint32_t before = scan[max(w[j] - 1, 0)];
+    ref[j] = src.at(p0, w[j], (int64_t)sbeg[w[j]] + (e[j] - (w[j] ? before : 0u)));
+  }
+#pragma unroll
+  for (int j = 0; j < U; ++j) li[j] = src.pos(ref[j]);
+  if (val16) {
+    uint16_t hv[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) hv[j] = src.half(ref[j]);
+#pragma unroll
+    for (int j = 0; j < U; ++j) vv[j] = __half2float(__ushort_as_half(hv[j]));
+  } else {
+#pragma unroll
+    for (int j = 0; j < U; ++j) vv[j] = src.full(ref[j]);
+  }
+#pragma unroll
+  for (int j = 0; j < U; ++j)
+    li[j] = q0 + j * kUBlock + threadIdx.x < total ? li[j] - base : -1;
+}
+
 template <bool kTable>
 __device__ __forceinline__ void load_pairs(const PairSrc<kTable>& src, const uint32_t* scan,
                                            const int32_t* sbeg, int p0, uint32_t q0,
                                            uint32_t total, int32_t base, int val16,
                                            int32_t (&li)[kPairUnroll],
                                            float (&vv)[kPairUnroll]) {
-  uint32_t e[kPairUnroll];
-  int w[kPairUnroll];
-#pragma unroll
-  for (int j = 0; j < kPairUnroll; ++j)
-    e[j] = min(q0 + j * kUBlock + threadIdx.x, total - 1u);
-  entry_workers(scan, e, w);
-  typename PairSrc<kTable>::Ref ref[kPairUnroll];
 #pragma unroll
   for (int j = 0; j < kPairUnroll; ++j) {
-    const uint32_t before = scan[max(w[j] - 1, 0)];
-    ref[j] = src.at(p0, w[j], (int64_t)sbeg[w[j]] + (e[j] - (w[j] ? before : 0u)));
+    li[j] = -1;
+    vv[j] = 0.0f;
   }
-#pragma unroll
-  for (int j = 0; j < kPairUnroll; ++j) li[j] = src.pos(ref[j]);
-  if (val16) {
-    uint16_t hv[kPairUnroll];
-#pragma unroll
-    for (int j = 0; j < kPairUnroll; ++j) hv[j] = src.half(ref[j]);
-#pragma unroll
-    for (int j = 0; j < kPairUnroll; ++j) vv[j] = __half2float(__ushort_as_half(hv[j]));
-  } else {
-#pragma unroll
-    for (int j = 0; j < kPairUnroll; ++j) vv[j] = src.full(ref[j]);
-  }
-#pragma unroll
-  for (int j = 0; j < kPairUnroll; ++j)
-    li[j] = q0 + j * kUBlock + threadIdx.x < total ? li[j] - base : -1;
+  if (q0 + (threadIdx.x & ~63u) >= total) return;
+  if (total - q0 <= (uint32_t)kUBlock)
+    load_pairs_of<1, kTable>(src, scan, sbeg, p0, q0, total, base, val16, li, vv);
+  else
+    load_pairs_of<kPairUnroll, kTable>(src, scan, sbeg, p0, q0, total, base, val16, li, vv);
 }
 
 // The ordered accumulation of one chunk of list entries (deterministic mode).
@@ -3405,21 +3431,21 @@ int32_t emit_lds_groups() { return kEmitLdsGroups; }
 hipError_t launch_seg(const int32_t* idx, int64_t stride, const int32_t* nnz, int32_t P,
                       int32_t d, int32_t ntiles_u, int32_t* seg, uint32_t* status,
                       hipStream_t s, const Ev& ev) {
-  int64_t bx = (stride + 256 * kSegPer - 1) / (256 * kSegPer);
-  if (bx < 1) bx = 1;
+  const int per = (int64_t)P * stride > kSegFew ? 2 : 1;
+  const int64_t bx = std::max<int64_t>(1, (stride + 256 * per - 1) / (256 * per));
   const ListsArg lists{idx, nullptr, stride, nnz, nullptr};
-  return launch(k_seg<false>, dim3((unsigned)bx, (unsigned)P), dim3(256), s, ev, lists, P, d,
-                ntiles_u, seg, status);
+  return launch(per == 2 ? k_seg<false, 2> : k_seg<false, 1>, dim3((unsigned)bx, (unsigned)P),
+                dim3(256), s, ev, lists, P, d, ntiles_u, seg, status);
 }
 
 hipError_t launch_seg_table(const WorkerList* table, int32_t P, int64_t max_n, int32_t d,
                             int32_t ntiles_u, int32_t* seg, uint32_t* status, hipStream_t s,
                             const Ev& ev) {
-  int64_t bx = (max_n + 256 * kSegPer - 1) / (256 * kSegPer);
-  if (bx < 1) bx = 1;
+  const int per = (int64_t)P * max_n > kSegFew ? 2 : 1;
+  const int64_t bx = std::max<int64_t>(1, (max_n + 256 * per - 1) / (256 * per));
   const ListsArg lists{nullptr, nullptr, 0, nullptr, table};
-  return launch(k_seg<true>, dim3((unsigned)bx, (unsigned)P), dim3(256), s, ev, lists, P, d,
-                ntiles_u, seg, status);
+  return launch(per == 2 ? k_seg<true, 2> : k_seg<true, 1>, dim3((unsigned)bx, (unsigned)P),
+                dim3(256), s, ev, lists, P, d, ntiles_u, seg, status);
 }
 
 // whole groups of kXcds runs (workgroups past the last tile return at once)
