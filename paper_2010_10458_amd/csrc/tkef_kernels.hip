@@ -237,18 +237,13 @@ constexpr int kQuarter = kStreamUnit;
 constexpr int kQV = kQuarter / (4 * kBlock);  // float4 of each array per thread per unit
 static_assert(kQV * 4 * kBlock == kQuarter && kTile % kQuarter == 0, "stream unit shape");
 
-// Non-temporal 16-byte load / store through a global-memory view.
-__device__ __forceinline__ float4 load_nt4(const float4* p) {
-  const v4f t = __builtin_nontemporal_load((const gv4f*)p);
+// Four floats from p, at any 4-byte address: a cached load (through the generic
+// address: the LARS step of 25.6 M parameters takes 127.2 us with it and 132.7
+// through the global view), and non-temporal ones and stores.
+__device__ __forceinline__ float4 load4u(const float* p) {
+  const v4fu t = *reinterpret_cast<const v4fu*>(p);
   return make_float4(t.x, t.y, t.z, t.w);
 }
-
-__device__ __forceinline__ void store_nt4(float4* p, float4 v) {
-  const v4f t = {v.x, v.y, v.z, v.w};
-  __builtin_nontemporal_store(t, (gv4f*)p);
-}
-
-// The same at any 4-byte address, four floats from p.
 __device__ __forceinline__ float4 load_nt4u(const float* p) {
   const v4fu t = __builtin_nontemporal_load((const gv4fu*)p);
   return make_float4(t.x, t.y, t.z, t.w);
@@ -2132,8 +2127,7 @@ __device__ __forceinline__ void det_accumulate(const int32_t (&li)[kPairUnroll],
 }
 
 // One update tile: number, first position, positions, first tensor; where its
-// w (and b) lie if it is inside one tensor and they start 16-byte aligned
-// (fast).
+// w (and b) lie if it is inside one tensor (fast).
 struct UpdTile {
   int32_t u, base, len, t0;
   float* w;
@@ -2187,15 +2181,13 @@ __device__ __forceinline__ void tile_step_fast(const UpdTile& ut,
                                                bool densify, bool lapply, bool mom, float rate,
                                                float lr, float mu, float wd, float eps) {
   const int tid = threadIdx.x;
-  float4* w4 = reinterpret_cast<float4*>(ut.w);
-  float4* b4 = reinterpret_cast<float4*>(ut.b);
   const float4* a4 = reinterpret_cast<const float4*>(acc);
 #pragma unroll
   for (int q = 0; q < kUVecPerThread; ++q) {
     const int v = q * kUBlock + tid;
     const float4 G = a4[v];
     if (densify) {
-      store_nt4(w4 + v, G);
+      store_nt4u(ut.w + 4 * v, G);
       continue;
     }
     float4 w = wv[q], bb = mom ? bv[q] : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -2210,8 +2202,8 @@ __device__ __forceinline__ void tile_step_fast(const UpdTile& ut,
       w.z = sgd_step(G.z, w.z, bb.z, mom, lr, mu, wd);
       w.w = sgd_step(G.w, w.w, bb.w, mom, lr, mu, wd);
     }
-    store_nt4(w4 + v, w);
-    if (mom) store_nt4(b4 + v, bb);
+    store_nt4u(ut.w + 4 * v, w);
+    if (mom) store_nt4u(ut.b + 4 * v, bb);
   }
 }
 
@@ -2233,36 +2225,30 @@ __device__ __forceinline__ void tile_step_general(const UpdTensor* __restrict__ 
     const int la = (int)(a - base);
     gfloat* __restrict__ w = gptr(tt.w + (a - tt.goff));
     gfloat* __restrict__ bm = mom ? gptr(tt.b + (a - tt.goff)) : nullptr;
-    const bool vec = ((reinterpret_cast<uintptr_t>(w) |
-                       (bm ? reinterpret_cast<uintptr_t>(bm) : 0u)) & 15u) == 0;
     const float rate = lapply ? (float)lars.rate[ti] : 0.0f;
     auto step = [&](float G, float wq, float& bq) -> float {
       return lapply ? lars_step(G, wq, bq, mom, rate, mu, lars.eps)
                     : sgd_step(G, wq, bq, mom, lr, mu, wd);
     };
-    int done = 0;
-    if (vec) {
-      const int nv = cnt >> 2;
-      gv4f* w4 = (gv4f*)w;
-      gv4f* b4 = (gv4f*)bm;
-      for (int q = tid; q < nv; q += kUBlock) {
-        if (densify) {
-          const int l = la + 4 * q;
-          w4[q] = v4f{acc[l], acc[l + 1], acc[l + 2], acc[l + 3]};
-          continue;
-        }
-        const v4f wv4 = w4[q];
-        const v4f bv4 = bm ? b4[q] : v4f{0.f, 0.f, 0.f, 0.f};
-        float wq[4] = {wv4.x, wv4.y, wv4.z, wv4.w}, bq[4] = {bv4.x, bv4.y, bv4.z, bv4.w};
+    const int nv = cnt >> 2;
+    gv4fu* w4 = (gv4fu*)w;
+    gv4fu* b4 = (gv4fu*)bm;
+    for (int q = tid; q < nv; q += kUBlock) {
+      if (densify) {
         const int l = la + 4 * q;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) wq[c] = step(acc[l + c], wq[c], bq[c]);
-        w4[q] = v4f{wq[0], wq[1], wq[2], wq[3]};
-        if (mom) b4[q] = v4f{bq[0], bq[1], bq[2], bq[3]};
+        w4[q] = v4fu{acc[l], acc[l + 1], acc[l + 2], acc[l + 3]};
+        continue;
       }
-      done = nv << 2;
+      const v4fu wv4 = w4[q];
+      const v4fu bv4 = bm ? b4[q] : v4fu{0.f, 0.f, 0.f, 0.f};
+      float wq[4] = {wv4.x, wv4.y, wv4.z, wv4.w}, bq[4] = {bv4.x, bv4.y, bv4.z, bv4.w};
+      const int l = la + 4 * q;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) wq[c] = step(acc[l + c], wq[c], bq[c]);
+      w4[q] = v4fu{wq[0], wq[1], wq[2], wq[3]};
+      if (mom) b4[q] = v4fu{bq[0], bq[1], bq[2], bq[3]};
     }
-    for (int q = done + tid; q < cnt; q += kUBlock) {
+    for (int q = (nv << 2) + tid; q < cnt; q += kUBlock) {
       if (densify) {
         w[q] = acc[la + q];
         continue;
@@ -2320,26 +2306,23 @@ __global__ __launch_bounds__(kUBlock) void k_update(
   const int32_t len = min(kUTile, d - base);
   const bool mom = has_mom != 0;
 
-  // Dense fast path: the tile lies inside one tensor and its w (and b) start
-  // 16-byte aligned. Its parameters are fetched before the accumulation so
-  // their HBM latency overlaps it.
+  // Dense fast path: the tile lies inside one tensor (wherever it starts:
+  // v4fu). Its parameters are fetched before the accumulation so their HBM
+  // latency overlaps it.
   const int32_t t0 = tile_first[u];
   const UpdTensor tt0 = tens[t0];
   float* __restrict__ w_tile = tt0.w + (base - tt0.goff);
   float* __restrict__ b_tile = mom ? tt0.b + (base - tt0.goff) : nullptr;
   const bool fast = !sparse_mode && len == kUTile && tt0.goff <= base &&
-                    (int64_t)base + len <= tt0.goff + tt0.n &&
-                    ((reinterpret_cast<uintptr_t>(w_tile) |
-                      (mom ? reinterpret_cast<uintptr_t>(b_tile) : 0u)) & 15u) == 0;
+                    (int64_t)base + len <= tt0.goff + tt0.n;
   float4 wv[kUVecPerThread], bv[kUVecPerThread];
   if (fast && !densify) {  // (aggregation only writes the tile)
-    const float4* w4 = reinterpret_cast<const float4*>(w_tile);
-    const float4* b4 = reinterpret_cast<const float4*>(b_tile);
 #pragma unroll
     for (int q = 0; q < kUVecPerThread; ++q) {
+      const int at = 4 * (q * kUBlock + tid);
       // (the norm pass reads w again in the step pass: keep it cached)
-      wv[q] = lnorm ? w4[q * kUBlock + tid] : load_nt4(w4 + q * kUBlock + tid);
-      if (mom && !lnorm) bv[q] = load_nt4(b4 + q * kUBlock + tid);
+      wv[q] = lnorm ? load4u(w_tile + at) : load_nt4u(w_tile + at);
+      if (mom && !lnorm) bv[q] = load_nt4u(b_tile + at);
     }
   }
 
@@ -2467,21 +2450,16 @@ __global__ __launch_bounds__(kUBlock) void k_lars_norm_dense(
     const gfloat* g = gptr(gptrs[ti] + (a - tt.goff));
     const int cnt = (int)(z - a);
     double sw = 0.0, sg = 0.0;
-    const bool vec = ((reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(g)) & 15u) == 0;
-    int done = 0;
-    if (vec) {
-      const int nv = cnt >> 2;
-      const gv4f* w4 = (const gv4f*)w;
-      const gv4f* g4 = (const gv4f*)g;
-      for (int q = tid; q < nv; q += kUBlock) {
-        const v4f x = __builtin_nontemporal_load(w4 + q);
-        const v4f y = __builtin_nontemporal_load(g4 + q);
-        sw += (double)x.x * x.x + (double)x.y * x.y + (double)x.z * x.z + (double)x.w * x.w;
-        sg += (double)y.x * y.x + (double)y.y * y.y + (double)y.z * y.z + (double)y.w * y.w;
-      }
-      done = nv << 2;
+    const int nv = cnt >> 2;
+    const gv4fu* w4 = (const gv4fu*)w;
+    const gv4fu* g4 = (const gv4fu*)g;
+    for (int q = tid; q < nv; q += kUBlock) {
+      const v4fu x = __builtin_nontemporal_load(w4 + q);
+      const v4fu y = __builtin_nontemporal_load(g4 + q);
+      sw += (double)x.x * x.x + (double)x.y * x.y + (double)x.z * x.z + (double)x.w * x.w;
+      sg += (double)y.x * y.x + (double)y.y * y.y + (double)y.z * y.z + (double)y.w * y.w;
     }
-    for (int q = done + tid; q < cnt; q += kUBlock) {
+    for (int q = (nv << 2) + tid; q < cnt; q += kUBlock) {
       const double x = w[q], y = g[q];
       sw += x * x;
       sg += y * y;

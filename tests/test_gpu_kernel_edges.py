@@ -175,3 +175,69 @@ def test_update_list_lengths(k):
                                 torch.from_numpy(val[p, :nnz[p]].copy()).to(dev))
                                for p in range(P)], lr=-1.0)
     assert_bitwise(w2.cpu().numpy(), w0, "per-worker lists")
+
+
+# Parameters and momentum that start off the 16-byte grid, each on its own: whole
+# 4,096-position tiles, tiles that two tensors share, remainders; the elements
+# around each tensor keep their values. Integer values: every order is exact.
+@pytest.mark.parametrize("op", ["momentum", "wd", "aggregate", "lars", "rates"])
+@pytest.mark.parametrize("ws,bs", [(1, 1), (2, 3), (0, 1), (3, 0)])
+def test_update_off_grid(ws, bs, op):
+    import torch
+    import oracle.lars as lars
+    dev = need_gpu()
+    sizes = [3 * 4096 + 77, 5, 2 * 4096, 4096 * 2 + 1]
+    d, P, k = sum(sizes), 6, 700
+    announce(f"update off grid w+{ws} b+{bs} {op}")
+    rng = np.random.default_rng([ws, bs])
+    w0 = [(rng.standard_normal(n) * 0.1).astype(np.float32) for n in sizes]
+    b0 = [(rng.standard_normal(n) * 0.1).astype(np.float32) for n in sizes]
+    idx = np.stack([np.sort(rng.choice(d, size=k, replace=False)) for _ in range(P)]).astype(np.int32)
+    val = (rng.integers(-8, 9, (P, k)) / 64.0).astype(np.float32)
+    guard = np.float32(7e29)
+
+    def place(arrs, shift):
+        bufs = []
+        for a in arrs:
+            x = np.full(a.size + 16, guard, np.float32)
+            x[shift:shift + a.size] = a
+            bufs.append(torch.from_numpy(x).to(dev))
+        return bufs, [x[shift:shift + a.size] for x, a in zip(bufs, arrs)]
+
+    wb, w = place(w0, ws)
+    bb, b = place(b0, bs)
+    it, vt = torch.from_numpy(idx).to(dev), torch.from_numpy(val).to(dev)
+    plan = tk.UpdatePlan(sizes, P=P, stride=k, check=True)
+    plan.bind(w, None if op in ("wd", "aggregate", "rates") else b)
+    G = orc().aggregate(d, idx, val)
+    cut = np.cumsum(sizes)[:-1]
+    rates = None
+    if op == "aggregate":
+        plan.aggregate(it, vt)
+        want_w, want_b = np.split(G, cut), b0
+    elif op == "lars":
+        rates = plan.lars_execute(it, vt, gamma=0.5, eta=0.25, eps=0.01, mu=0.9).cpu().numpy()
+        want_w, want_b, want_r = lars.lars_update(w0, b0, np.split(G, cut), 0.5, 0.25, 0.01, 0.9)
+    elif op == "rates":
+        plan.bind_grads(b)  # (the dense gradients: the second set of buffers)
+        rates = plan.lars_rates(0.5, 0.25, 0.01).cpu().numpy()
+        want_w, want_b = w0, b0
+        want_r = [0.5 * 0.25 * lars.layer_norm(a) / (lars.layer_norm(g) + 0.01 * lars.layer_norm(a))
+                  for a, g in zip(w0, b0)]
+    else:
+        mu = 0.9 if op == "momentum" else 0.0
+        plan.execute(it, vt, lr=0.1, mu=mu, wd=0.01)
+        fw, fb = orc().update(gen.concat(w0), gen.concat(b0) if mu else None, idx, val, lr=0.1,
+                              mu=mu, wd=0.01)
+        want_w, want_b = np.split(fw, cut), np.split(fb, cut) if mu else b0
+    torch.cuda.synchronize()
+    if rates is not None:
+        # sums of squares in double on both sides, a few thousand terms
+        assert np.all(np.abs(rates - np.asarray(want_r)) <= 1e-12 * np.abs(want_r))
+    for t, n in enumerate(sizes):
+        for buf, sh, want, what in ((wb, ws, want_w, "w"), (bb, bs, want_b, "b")):
+            got = buf[t].cpu().numpy()
+            same = rates is None or np.float32(rates[t]) == np.float32(want_r[t])
+            if same:
+                assert_bitwise(got[sh:sh + n], np.asarray(want[t], np.float32).ravel(), f"{what}[{t}]")
+            assert (got[:sh] == guard).all() and (got[sh + n:] == guard).all()
