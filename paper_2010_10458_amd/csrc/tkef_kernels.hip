@@ -668,6 +668,19 @@ struct LineSpan {
     t = tiles[tile];
     lim = has ? lpt : 0;
   }
+  // The same for any power of two lines up to MAXL: one summary at a time.
+  __device__ __forceinline__ void load_any(const TileDesc* __restrict__ tiles,
+                                           const uint16_t* __restrict__ summ, int64_t nlines,
+                                           int64_t l0, int n) {
+    lim = l0 < nlines ? n : 0;  // (l0 and nlines are multiples of n)
+    tile = lim ? (int)(l0 / kLinesPerTile) : 0;
+    e0 = (int)(l0 % kLinesPerTile) * kLine;
+#pragma unroll
+    for (int q = 0; q < MAXL; q += 2)
+      sp[q / 2] = (q < lim ? (uint32_t)summ[l0 + q] : 0u) |
+                  (q + 1 < lim ? (uint32_t)summ[l0 + q + 1] : 0u) << 16;
+    t = tiles[tile];
+  }
   __device__ __forceinline__ int e0_of(int q) const { return e0 + q * kLine; }
   template <typename Thr>
   __device__ __forceinline__ uint32_t flagged(Thr thr) const {
@@ -1245,30 +1258,96 @@ __global__ __launch_bounds__(NT, 4) void k_finish(
     }
   }
   // class-2 members of the regions without stored band keys: from the lines
-  // of those that hold any (their count is known from rsuf)
+  // of those that hold any (their count is known from rsuf). Every workgroup reads
+  // all such lines, so the walk is bound by the L2. It only counts, in any order,
+  // and takes neighbouring regions as one run of lines, eight lanes to a line and
+  // kWalk lines per eight lanes at a time, so that all threads have lines however
+  // short a region is. f(keys, hits) is called by whole wavefronts; bit c of hits:
+  // key c is a member.
+  // (Equal magnitudes, the whole selection, region by region with a thread's lpt
+  // lines one after another, and now: 1 M elements, rho = 0.01, 62 regions, 4.40 ->
+  // 0.78 ms; 3.2 M, 187 regions, 13.3 -> 2.25; 25.6 M, rho = 0.001, 256 regions, 46.3
+  // -> 16.5; 2^27 with 5 % of one magnitude 10.2 -> 4.5. Two lines at a time: 0.90,
+  // 2.68, 19.9 and 4.65.)
   const uint32_t thr2 = cls21 << kH2Shift;
-  auto in_cls2 = [&](int, uint32_t key) -> bool { return (key >> kH2Shift) == cls21; };
   auto lines_class2 = [&](int wlim, auto f) {
+    constexpr int kWalk = 4;
+    constexpr int kPer = NT / 8;  // lines of a step
+    const int nl = (int)nlines, e = (tid & 7) * 4;
 #pragma unroll 1
     for (int wi = 0; wi * 32 < wlim; ++wi) {
       uint32_t m = c2bits[wi];
+      if (wlim - wi * 32 < 32) m &= (1u << (wlim - wi * 32)) - 1u;
 #pragma unroll 1
       while (m) {
-        const int r = wi * 32 + __ffs(m) - 1;
-        m &= m - 1u;
-        if (r >= wlim) break;
+        const int b = __ffs(m) - 1;
+        const uint32_t end = m + (1u << b);  // (carries through the run's bits)
+        const int z = end ? __ffs(end) - 1 : 32;
+        m &= end;
+        const int l1 = (int)min((int64_t)nl, (int64_t)(wi * 32 + z) * rl);
 #pragma unroll 1
-        for (int32_t s0 = 0; s0 < rl; s0 += NT * lpt) {
-          LineSpan lr;
-          lr.load(tiles, summ, min(nlines, (int64_t)(r + 1) * rl),
-                  (int64_t)r * rl + s0 + tid * lpt, lpt);
-          walk_mask(lr, lr.flagged([&](int) -> uint32_t { return thr2; }), in_cls2,
-                    [&](int, const TileDesc&, int, float, uint32_t key) { f(key); });
+        for (int l = (wi * 32 + b) * rl; l < l1; l += kWalk * kPer) {
+          uint32_t sv[kWalk];
+          const float* p[kWalk];
+          int n[kWalk];
+#pragma unroll
+          for (int q = 0; q < kWalk; ++q) {
+            const int i = l + q * kPer + (tid >> 3), ic = min(i, l1 - 1);
+            const TileDesc& t = tiles[ic / kLinesPerTile];
+            const int at = (ic % kLinesPerTile) * kLine + e;
+            sv[q] = i < l1 ? summ[ic] : 0u;
+            p[q] = t.r + at;
+            n[q] = i < l1 ? t.len - at : 0;
+          }
+          float4 v[kWalk];
+          bool part = false;
+#pragma unroll
+          for (int q = 0; q < kWalk; ++q) {
+            if (sv[q] < thr2 >> 16) n[q] = 0;
+            // (no branch between the loads: a lane without four elements reads the
+            // tile table)
+            const float* src = n[q] >= 4 ? p[q] : reinterpret_cast<const float*>(tiles);
+            const v4fu x = *(const gv4fu*)src;
+            v[q] = make_float4(x.x, x.y, x.z, x.w);
+            part |= n[q] > 0 && n[q] < 4;
+          }
+          if (__any(part)) {  // (the end of a tensor)
+#pragma unroll
+            for (int q = 0; q < kWalk; ++q) {
+              if (n[q] <= 0 || n[q] >= 4) continue;
+              const gfloat* g = gptr(p[q]);
+              v[q] = make_float4(g[0], n[q] > 1 ? g[1] : 0.f, n[q] > 2 ? g[2] : 0.f, 0.f);
+            }
+          }
+#pragma unroll
+          for (int q = 0; q < kWalk; ++q) {
+            const uint32_t key[4] = {mag_key(v[q].x), mag_key(v[q].y), mag_key(v[q].z),
+                                     mag_key(v[q].w)};
+            uint32_t hits = 0u;
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+              hits |= c < n[q] && (key[c] >> kH2Shift) == cls21 ? 1u << c : 0u;
+            f(key, hits);
+          }
         }
       }
     }
   };
-  lines_class2(G, [&](uint32_t key) { atomicAdd(&h[key & (kH3Bins - 1)], 1u); });
+  // (ties: the bin of a wavefront's first member is added once for all of them)
+  lines_class2(G, [&](const uint32_t (&key)[4], uint32_t hits) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const uint32_t bin = key[c] & (kH3Bins - 1);
+      const bool hit = (hits >> c & 1u) != 0u;
+      const uint64_t any = __ballot(hit);
+      if (!any) continue;
+      const int lead = __ffsll((unsigned long long)any) - 1;
+      const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)bin, lead);
+      const uint64_t same = __ballot(hit && bin == first);
+      if ((tid & 63) == lead) atomicAdd(&h[first], (uint32_t)__popcll(same));
+      else if (hit && bin != first) atomicAdd(&h[bin], 1u);
+    }
+  });
   __syncthreads();
   block_pick<NT, kH3Bins, 1>(h, need2, wsum, res);
   const uint32_t T = (cls21 << 10) | res[0];
@@ -1286,7 +1365,11 @@ __global__ __launch_bounds__(NT, 4) void k_finish(
   } else {
     for_class2<NT>(w, B2, rcap, rcnt, rsuf, rband, off, abv, wsum, tally);
   }
-  lines_class2(w, tally);
+  lines_class2(w, [&](const uint32_t (&key)[4], uint32_t hits) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (hits >> c & 1u) tally(key[c]);
+  });
 
   // this region's stored candidate (at most one per thread): counts of (key >
   // T) and (key == T) in position order (the rounds, and a region without
@@ -1362,15 +1445,20 @@ __global__ __launch_bounds__(NT, 4) void k_finish(
       cur = nxt;
     }
   } else if (own_ov) {
-    // from its lines, block by block: counts, then places
+    // from its lines, block by block: counts, then places. A thread takes lw lines,
+    // fewer than lpt in a region of fewer than NT * lpt lines, so that all threads
+    // have some (256 K elements, 5 % of one magnitude, rho = 0.01: the selection 122
+    // -> 93 us).
+    int lw = 1;
+    while (lw < lpt && NT * lw < rl) lw *= 2;
     uint32_t gtr_r = tot[2], eqr_r = tot[3];
     const uint32_t first = gtr_r + min(eqr_r, need3);
     auto at_least_T = [&](int, uint32_t key) -> bool { return key >= T; };
 #pragma unroll 1
-    for (int32_t s0 = 0; s0 < rl; s0 += NT * lpt) {
+    for (int32_t s0 = 0; s0 < rl; s0 += NT * lw) {
       LineSpan ls;
-      ls.load(tiles, summ, min(nlines, (int64_t)(w + 1) * rl), (int64_t)w * rl + s0 + tid * lpt,
-              lpt);
+      ls.load_any(tiles, summ, min(nlines, (int64_t)(w + 1) * rl),
+                  (int64_t)w * rl + s0 + tid * lw, lw);
       const uint32_t mask = ls.flagged([&](int) -> uint32_t { return T; });
       gt = eq = 0u;
       walk_mask(ls, mask, at_least_T,

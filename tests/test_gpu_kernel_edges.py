@@ -6,7 +6,8 @@ import pytest
 import gen
 import oracle
 import paper_2010_10458_amd as tk
-from gpu_common import announce, assert_bitwise, need_gpu, to_dev, to_host
+import region_layout
+from gpu_common import announce, assert_bitwise, check_selection, need_gpu, to_dev, to_host
 from test_gpu_update_det import det_update_vs_oracle
 
 pytestmark = pytest.mark.gpu
@@ -121,6 +122,77 @@ def test_sparsify_regions_of_blocks_over_capacity():
     assert torch.equal(val, g[want])
     g[want] = 0.0
     assert torch.equal(r, g)
+
+
+# Regions that cannot store their band (the finish reads their lines, neighbours as
+# one run): alone, at the ends, in runs that cross the 32 regions of a mask
+# word, every other one; regions of fewer lines than threads times lines per
+# thread, tensors that end within a line, and 1,024-thread workgroups. The band's
+# members take 40 magnitudes, so the threshold's are split by position.
+RUNS = {"first": [0], "three": [3, 4, 5], "word": [30, 31, 32, 33], "apart": [1, 3, 5, 40],
+        "word_ends": [0, 31, 32, 61], "all": list(range(62))}
+
+
+@pytest.mark.parametrize("sizes,k,runs", [([1 << 20], 10_486, r) for r in RUNS] +
+                         [([700_001, 33, 300_000, 48_543], 10_486, r) for r in ("three", "all")] +
+                         [([300_007], 3001, "three"), ([34_000_000], 34_000, "word")])
+def test_unstored_region_runs(sizes, k, runs):
+    import torch
+    dev = need_gpu()
+    d, a = sum(sizes), region_layout.layout(sizes, k)
+    ids = [r for r in RUNS[runs] if r < a["count"] - 1]
+    announce(f"unstored regions {runs} d={d} k={k}")
+    rng = np.random.default_rng([d, len(ids)])
+    x = (rng.standard_normal(d, dtype=np.float32) * np.float32(0.1))
+    top = rng.choice(d, k // 2, replace=False)
+    x[top] = (10 + rng.random(top.size)) * rng.choice([-1, 1], top.size)
+    vals = (5 + 0.49 * rng.random(40)).astype(np.float32)   # (one level-1 bin)
+    where = region_layout.region_of(sizes, k)
+    fill = max(a["rcap"] + 900, -(-k // len(ids)))  # (the threshold is among them)
+    for r in ids:
+        own = np.flatnonzero(where == r)
+        pos = rng.choice(own, min(fill, own.size), replace=False)
+        x[pos] = rng.choice(vals, pos.size) * rng.choice([-1, 1], pos.size).astype(np.float32)
+    _, band = region_layout.counts(x, sizes, k)
+    assert list(np.flatnonzero(band > a["rcap"])) == ids
+    cuts = np.cumsum(sizes)[:-1]
+    g, r = to_dev(np.split(x, cuts), dev), [torch.zeros(n, device=dev) for n in sizes]
+    status = torch.zeros(1, dtype=torch.int32, device=dev)
+    plan = tk.SparsifyPlan(sizes, k=k).bind(g, r)
+    for _ in range(2):  # (the second run starts from the scratch the first left)
+        for t in r:
+            t.zero_()
+        idx, val = plan.execute(status=status)
+        torch.cuda.synchronize()
+        assert int(status.item()) == 0
+        check_selection(orc().ef_add(x, np.zeros(d, np.float32)), idx.cpu().numpy(),
+                        val.cpu().numpy(), gen.concat(to_host(r)), k)
+
+
+# The time of that path follows the lines it reads, not how they are split: equal
+# magnitudes at rho = 0.001 (49 regions) and 0.01 (187) read the same ones. (2.8
+# times as long when each region was walked by itself, 1.0 as runs.)
+def test_unstored_regions_time_follows_lines():
+    import torch
+    dev = need_gpu()
+    announce("equal magnitudes, two region splits, timed")
+    d = 3_194_629
+    g = torch.ones(d, device=dev)
+    times = []
+    for rho in (0.001, 0.01):
+        r = torch.zeros(d, device=dev)
+        plan = tk.SparsifyPlan([d], rho=rho).bind([g], [r])
+        best = float("inf")
+        for _ in range(6):
+            r.zero_()
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ev[0].record()
+            plan.execute()
+            ev[1].record()
+            torch.cuda.synchronize()
+            best = min(best, ev[0].elapsed_time(ev[1]))
+        times.append(best)
+    assert times[1] < 1.7 * times[0], times
 
 
 # Region splits: as many regions as there can be, a last one of a few lines, one
