@@ -1983,24 +1983,37 @@ constexpr int kUVecPerThread = kUTile / 4 / kUBlock;  // float4 per thread per t
 
 constexpr int kPairUnroll = 3;  // list entries per thread and chunk of the accumulation
 
-// The workers of a thread's entries e[] of a tile: the first w with scan[w] >
-// e, scan the inclusive prefix of the workers' counts in the tile (kUBlock
-// words, the last above every e). A fixed number of steps, the searches side
-// by side, so that their LDS reads overlap.
+// The workers of a thread's entries e[] of a tile: the first w < nw with scan[w]
+// > e, scan the inclusive prefix of the workers' counts in the tile (kUBlock
+// words, the last above every e; nw <= kUBlock workers). Without a branch on
+// the found values, the searches side by side, so that their LDS reads overlap.
+// With one entry per thread (few entries) the search is a chain that the tile
+// waits for, and takes log2(nw) steps instead of eight: sums over 25.6 M
+// positions, k_update, P = 1 list 23.3 -> 22.2 us (a branching search by the
+// threads that have an entry: 22.5), P = 8 25.0 -> 24.2 (24.2), P = 16 25.6 -> 25.3
+// (24.9); plain update, P = 1, 17.4 -> 16.6. With several entries the steps are
+// fixed, for the unrolled loop's sake.
 template <int U>
-__device__ __forceinline__ void entry_workers(const uint32_t* scan,
-                                              const uint32_t (&e)[U],
-                                              int (&w)[U]) {
+__device__ __forceinline__ void entry_workers(const uint32_t* scan, uint32_t nw,
+                                              const uint32_t (&e)[U], int (&w)[U]) {
 #pragma unroll
   for (int j = 0; j < U; ++j) w[j] = 0;
-#pragma unroll
-  for (int step = kUBlock / 2; step >= 1; step >>= 1) {
+  auto halve = [&](uint32_t step) {
     uint32_t s[U];
 #pragma unroll
     for (int j = 0; j < U; ++j) s[j] = scan[w[j] + step - 1];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < U; ++j) w[j] += s[j] <= e[j] ? step : 0;
+    for (int j = 0; j < U; ++j) w[j] += s[j] <= e[j] ? (int)step : 0;
+  };
+  if constexpr (U == 1) {
+    // (the largest power of two below nw; the words read end before 2 * it <= kUBlock)
+    uint32_t step = nw > 1u ? 0x80000000u >> __builtin_clz(nw - 1u) : 0u;
+#pragma unroll 1
+    for (; step; step >>= 1) halve(step);
+  } else {
+#pragma unroll
+    for (uint32_t step = kUBlock / 2; step >= 1; step >>= 1) halve(step);
   }
 }
 
@@ -2055,15 +2068,15 @@ struct PairSrc {
 // per thread always, 33.4 now).
 template <int U, bool kTable>
 __device__ __forceinline__ void load_pairs_of(const PairSrc<kTable>& src, const uint32_t* scan,
-                                              const int32_t* sbeg, int p0, uint32_t q0,
-                                              uint32_t total, int32_t base, int val16,
+                                              const int32_t* sbeg, int p0, uint32_t nw,
+                                              uint32_t q0, uint32_t total, int32_t base, int val16,
                                               int32_t (&li)[kPairUnroll],
                                               float (&vv)[kPairUnroll]) {
   uint32_t e[U];
   int w[U];
 #pragma unroll
   for (int j = 0; j < U; ++j) e[j] = min(q0 + j * kUBlock + threadIdx.x, total - 1u);
-  entry_workers<U>(scan, e, w);
+  entry_workers<U>(scan, nw, e, w);
   typename PairSrc<kTable>::Ref ref[U];
 #pragma unroll
   for (int j = 0; j < U; ++j) {
@@ -2089,8 +2102,8 @@ __device__ __forceinline__ void load_pairs_of(const PairSrc<kTable>& src, const 
 
 template <bool kTable>
 __device__ __forceinline__ void load_pairs(const PairSrc<kTable>& src, const uint32_t* scan,
-                                           const int32_t* sbeg, int p0, uint32_t q0,
-                                           uint32_t total, int32_t base, int val16,
+                                           const int32_t* sbeg, int p0, uint32_t nw,
+                                           uint32_t q0, uint32_t total, int32_t base, int val16,
                                            int32_t (&li)[kPairUnroll],
                                            float (&vv)[kPairUnroll]) {
 #pragma unroll
@@ -2100,9 +2113,9 @@ __device__ __forceinline__ void load_pairs(const PairSrc<kTable>& src, const uin
   }
   if (q0 + (threadIdx.x & ~63u) >= total) return;
   if (total - q0 <= (uint32_t)kUBlock)
-    load_pairs_of<1, kTable>(src, scan, sbeg, p0, q0, total, base, val16, li, vv);
+    load_pairs_of<1, kTable>(src, scan, sbeg, p0, nw, q0, total, base, val16, li, vv);
   else
-    load_pairs_of<kPairUnroll, kTable>(src, scan, sbeg, p0, q0, total, base, val16, li, vv);
+    load_pairs_of<kPairUnroll, kTable>(src, scan, sbeg, p0, nw, q0, total, base, val16, li, vv);
 }
 
 // The ordered accumulation of one chunk of list entries (deterministic mode).
@@ -2457,7 +2470,8 @@ __global__ __launch_bounds__(kUBlock) void k_update(
     for (uint32_t q0 = 0; q0 < total; q0 += kUBlock * kPairUnroll) {
       int32_t li[kPairUnroll];
       float vv[kPairUnroll];
-      load_pairs<kTable>(src, scan, sbeg, p0, q0, total, base, val16, li, vv);
+      load_pairs<kTable>(src, scan, sbeg, p0, (uint32_t)min(P - p0, kUBlock), q0, total, base,
+                         val16, li, vv);
       if constexpr (kDet) {
         det_accumulate(li, vv, len, sparse_mode, acc, mask, dcnt, dq, dv, &dtop);
       } else {

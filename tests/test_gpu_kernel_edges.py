@@ -249,6 +249,33 @@ def test_update_list_lengths(k):
     assert_bitwise(w2.cpu().numpy(), w0, "per-worker lists")
 
 
+# Entry search with few entries in a tile: worker counts around the powers of two
+# that its steps follow, up to a full batch of 256 workers and one beyond it; the
+# last workers alone have entries in the second tile. Integer values: exact sums.
+@pytest.mark.parametrize("P", [1, 2, 3, 4, 5, 8, 9, 127, 128, 129, 255, 256, 257, 300])
+@pytest.mark.parametrize("ordered", [False, True])
+def test_update_few_entries_many_workers(P, ordered):
+    import torch
+    dev = need_gpu()
+    announce(f"few entries P={P} ordered={ordered}")
+    d, k = 3 * 4096, 2
+    rng = np.random.default_rng(P)
+    idx = np.sort(rng.integers(0, 4096, (P, k)), axis=1)
+    idx[-1] = [4096 + 5, 8191]
+    idx[-(P // 2) - 1, 1] = 4096 + 7
+    nnz = np.where(np.arange(P) % 3 == 1, 0, k).astype(np.int32)  # (workers without entries)
+    nnz[-1] = k
+    val = rng.integers(-8, 9, (P, k)).astype(np.float32)
+    out = torch.zeros(d, device=dev)
+    plan = tk.UpdatePlan([d], P=P, stride=k, deterministic=ordered, check=True).bind([out])
+    plan.aggregate(torch.from_numpy(idx.astype(np.int32)).to(dev), torch.from_numpy(val).to(dev),
+                   nnz=torch.from_numpy(nnz).to(dev))
+    want = np.zeros(d, np.float32)
+    for p in range(P):
+        np.add.at(want, idx[p, :nnz[p]], val[p, :nnz[p]])
+    assert_bitwise(out.cpu().numpy(), want, "sums")
+
+
 # Parameters and momentum that start off the 16-byte grid, each on its own: whole
 # 4,096-position tiles, tiles that two tensors share, remainders; the elements
 # around each tensor keep their values. Integer values: every order is exact.
