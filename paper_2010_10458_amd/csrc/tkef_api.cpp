@@ -177,12 +177,13 @@ struct tkef_sparsify_plan_s {
 // d, ngroups, k_total, ntiles, nlines); allocates nothing. False when the
 // selection grids cannot cover the tiles.
 bool sparsify_layout(tkef_sparsify_plan_s* p) {
-  // selection kernels: `lpt` consecutive summary lines per thread, at most
-  // select_max_groups() workgroups of sb threads (collect_block() for the
-  // exact one-group kernels, select_block() for the others). Aim for about
-  // 256 workgroups (one per compute unit); lpt is a power of two from 4 up
-  // (the kernels fetch four 16-bit summaries per load, and a thread's lines
-  // must lie in one tile).
+  // selection kernels: `lpt` consecutive summary lines per thread, a power of two
+  // from 4 up (the kernels fetch four 16-bit summaries per load, and a thread's
+  // lines must lie in one tile), for about 256 workgroups (one per compute unit).
+  // The exact one-group kernels take regions of sel_rl lines in blocks of
+  // collect_block() * lpt, at most collect_regions() of them; the others have
+  // select_block() threads and one block of lines per workgroup, at most
+  // select_max_groups() of them.
   const bool one = p->ngroups == 1;
   const bool approx = p->mode == TKEF_APPROX;
   const bool coll = one && !approx;
@@ -192,16 +193,16 @@ bool sparsify_layout(tkef_sparsify_plan_s* p) {
   const int64_t want = (p->nlines + sb * 256 - 1) / (sb * 256);
   int64_t lpt = 4;  // a power of two from 4 to select_max_lpt()
   while (lpt < want && lpt < select_max_lpt()) lpt *= 2;
-  if ((p->nlines + sb * lpt - 1) / (sb * lpt) > sg) return false;  // (kMaxTiles)
+  if (!coll && (p->nlines + sb * lpt - 1) / (sb * lpt) > sg) return false;  // (kMaxTiles)
   p->sel_lpt = (int32_t)lpt;
   // one exact group: collect_regions() equal regions, or fewer, so that a region
   // holds about one round of flagged lines (256 of the half-size workgroup; at
-  // these densities up to 48 k of d lines hold a candidate), within one and four
-  // lines per thread: each region more costs every finish workgroup (4 M
-  // elements, rho = 0.001: 64 regions 8.0 + 5.4 us collect + finish, 256 regions
-  // 8.7 + 6.6), each round more costs collect (rho = 0.01: 256 K elements, 4
-  // regions 14.3 + 6.6, 16 regions 7.2 + 5.4; 1 M elements 14.9 + 7.1 and 8.9 +
-  // 5.7).
+  // these densities the share of lines that hold a candidate is up to 48 k / d),
+  // within one and four lines per thread: each region more costs every finish
+  // workgroup (4 M elements, rho = 0.001: 64 regions 8.0 + 5.4 us collect + finish,
+  // 256 regions 8.7 + 6.6), each round more costs collect (rho = 0.01: 256 K
+  // elements, 4 regions 14.3 + 6.6, 16 regions 7.2 + 5.4; 1 M elements 14.9 + 7.1
+  // and 8.9 + 5.7).
   int64_t rl = sb * lpt;
   if (coll) {
     const int64_t even = (p->nlines + collect_regions() - 1) / collect_regions();

@@ -465,10 +465,10 @@ __global__ __launch_bounds__(kBlock) void k_pick(int level, const GroupDesc* __r
 // ---------------------------------------------------------------------------
 // Selection kernels after the stream.
 //
-// They run as at most kSMaxGroups workgroups of kSBlock threads (collect and
-// finish: NT threads, see below), each thread owning `lpt` consecutive
-// summary lines (or, in the per-tensor emit and hist3, a run of the compacted
-// candidate list). A candidate is encoded as (tile << 13) | position-in-tile,
+// They run as at most kSMaxGroups workgroups of kSBlock threads, each thread
+// owning `lpt` consecutive summary lines or, in the per-tensor emit and hist3, a
+// run of the compacted candidate list (collect and finish: at most kFMaxGroups
+// workgroups of NT threads that walk their region in blocks, see below). A candidate is encoded as (tile << 13) | position-in-tile,
 // in the per-tensor list together with the bits of x.
 //
 // The per-tensor path places its ordered output with a prefix of
@@ -498,8 +498,7 @@ constexpr int kSMaxLpt = 16;     // lines per thread at most
 static_assert(kLinesPerTile % kSMaxLpt == 0, "a thread's lines lie in one tile");
 constexpr int kCandShift = 13;   // log2(kTile)
 static_assert((1 << kCandShift) == kTile, "candidate encoding");
-static_assert((int64_t)kSMaxGroups * kSBlock * kSMaxLpt >= kMaxTiles * kLinesPerTile &&
-              (int64_t)kSMaxGroups * kCBlockSmall * kSMaxLpt >= kCSmallLines,
+static_assert((int64_t)kSMaxGroups * kSBlock * kSMaxLpt >= kMaxTiles * kLinesPerTile,
               "the selection grids cover every tile of a list");
 constexpr uint64_t kFlagValid = 1ull << 63, kFlagVal = (1ull << 63) - 1;
 constexpr uint32_t kSpinLimit = 1u << 22;
@@ -1069,47 +1068,34 @@ __global__ __launch_bounds__(NT, 4) void k_collect(
   }
 }
 
-// Calls f(key) for the level-2 class members (band members in bin B2) of the
-// stored regions among [0, wlim), reading them again from rband. Regions are
-// taken NT at a time and their members spread over the workgroup through
-// a scan of the per-region counts. off, abv: NT words of LDS each.
-// Uniform in the workgroup.
+// Calls f(key, region) for the level-2 class members (band members in bin B2) of
+// the stored regions, read again from rband: `at` of them in region tid (0 for
+// threads without a region), after the `above` members of bins above B2. The
+// members are spread over the workgroup through a scan of the counts. off,
+// abv: kFMaxGroups words of LDS each. Uniform in the workgroup.
 template <int NT, typename F>
-__device__ __forceinline__ void for_class2(int wlim, uint32_t B2, uint32_t rcap,
-                                           const uint2* __restrict__ rcnt,
-                                           const uint32_t* __restrict__ rsuf,
+__device__ __forceinline__ void for_class2(uint32_t at, uint32_t above, uint32_t rcap,
                                            const uint32_t* __restrict__ rband, uint32_t* off,
                                            uint32_t* abv, uint32_t* wsum, F f) {
+  static_assert((kFMaxGroups & (kFMaxGroups - 1)) == 0 && kFMaxGroups <= NT, "search below");
   const int tid = threadIdx.x;
-#pragma unroll 1
-  for (int r0 = 0; r0 < wlim; r0 += NT) {
-    const int r = r0 + tid;
-    uint32_t above = 0u, at = 0u;
-    if (r < wlim) {
-      const uint2 cnt = rcnt[r];
-      const uint32_t bw = cnt.y & 0x7FFFFFFFu;
-      if (bw && !(cnt.y >> 31)) {
-        const uint32_t* sr = rsuf + (size_t)r * kH2Bins;
-        above = sr[B2];
-        at = (B2 ? sr[B2 - 1] : bw) - above;
-      }
-    }
-    uint32_t tot;
-    const uint32_t ex = block_scan<NT>(at, wsum, &tot);
+  uint32_t tot;
+  const uint32_t ex = block_scan<NT>(at, wsum, &tot);
+  if (tid < kFMaxGroups) {
     off[tid] = ex;
     abv[tid] = above;
-    __syncthreads();
-#pragma unroll 1
-    for (uint32_t j = tid; j < tot; j += NT) {
-      int a = 0, b = NT - 1;  // the last region slot with off <= j holds member j
-      while (a < b) {
-        const int m = (a + b + 1) >> 1;
-        if (off[m] <= j) a = m; else b = m - 1;
-      }
-      f(rband[(size_t)(r0 + a) * rcap + abv[a] + (j - off[a])]);
-    }
-    __syncthreads();
   }
+  __syncthreads();
+#pragma unroll 1
+  for (uint32_t j = tid; j < tot; j += NT) {
+    int a = 0, b = kFMaxGroups - 1;  // the last region with off <= j holds member j
+    while (a < b) {
+      const int m = (a + b + 1) >> 1;
+      if (off[m] <= j) a = m; else b = m - 1;
+    }
+    f(rband[(size_t)a * rcap + abv[a] + (j - off[a])], a);
+  }
+  __syncthreads();
 }
 
 template <int NT>
@@ -1126,7 +1112,7 @@ __global__ __launch_bounds__(NT, 4) void k_finish(
   __shared__ __align__(16) uint32_t h[kH3Bins];
   __shared__ uint32_t wsum[4 * (NT / 64)];
   __shared__ uint32_t res[3];
-  __shared__ uint32_t off[NT], abv[NT];
+  __shared__ uint32_t off[kFMaxGroups], abv[kFMaxGroups];
   __shared__ uint32_t ovbits[kOvWords];  // regions whose band keys were not stored
   __shared__ uint32_t c2bits[kOvWords];  // ... of them, those holding level-2 class members
   __shared__ uint32_t c2key[kC2Cap];     // level-2 class members of the stored regions
@@ -1177,7 +1163,8 @@ __global__ __launch_bounds__(NT, 4) void k_finish(
   // the counts that place it: per region, bw band members, `above` of them
   // in bins above B2 and `at` in bin B2, whose first kPerBin keys are in
   // rbin. gtb: this thread's share of the elements above T before region w.
-  uint32_t gtb = 0u;
+  // c2at, c2above: `at` and `above` of region tid, where its band is stored.
+  uint32_t gtb = 0u, c2at = 0u, c2above = 0u;
   bool slow = false;  // some region has more than kPerBin class-2 members
   if (tid < G) {
     const int r = tid;
@@ -1197,9 +1184,12 @@ __global__ __launch_bounds__(NT, 4) void k_finish(
       if (r < w) gtb += (cr.x & 0x7FFFFFFFu) - bw + above;
       if (ov) {
         if (at) atomicOr(&c2bits[r >> 5], 1u << (r & 31));  // its lines are walked below
-      } else if (at > (uint32_t)kPerBin) {
-        slow = true;
       } else {
+        c2at = at;
+        c2above = above;
+        slow = at > (uint32_t)kPerBin;
+      }
+      if (!ov && !slow) {
         const uint32_t ek[4] = {e.x, e.y, e.z, e.w};
 #pragma unroll
         for (int c = 0; c < kPerBin; ++c) {
@@ -1221,41 +1211,15 @@ __global__ __launch_bounds__(NT, 4) void k_finish(
     __syncthreads();  // every thread has read n2
     if (tid == 0) n2 = 0u;
     for (int i = tid; i < kH3Bins; i += NT) h[i] = 0u;
-#pragma unroll 1
-    for (int r0 = 0; r0 < G; r0 += NT) {
-      const int r = r0 + tid;
-      uint32_t above = 0u, at = 0u;
-      if (r < G) {
-        const uint2 cnt = rcnt[r];
-        const uint32_t bw = cnt.y & 0x7FFFFFFFu;
-        if (bw && !(cnt.y >> 31)) {
-          const uint32_t* sr = rsuf + (size_t)r * kH2Bins;
-          above = sr[B2];
-          at = (B2 ? sr[B2 - 1] : bw) - above;
-        }
+    // (for_class2's first barrier orders the reset)
+    for_class2<NT>(c2at, c2above, rcap, rband, off, abv, wsum, [&](uint32_t key, int r) {
+      atomicAdd(&h[key & (kH3Bins - 1)], 1u);
+      const uint32_t slot = atomicAdd(&n2, 1u);
+      if (slot < (uint32_t)kC2Cap) {
+        c2key[slot] = key;
+        c2reg[slot] = (uint16_t)r;
       }
-      uint32_t tot;
-      const uint32_t ex = block_scan<NT>(at, wsum, &tot);  // (its barriers order the reset above)
-      off[tid] = ex;
-      abv[tid] = above;
-      __syncthreads();
-#pragma unroll 1
-      for (uint32_t j = tid; j < tot; j += NT) {
-        int a = 0, b = NT - 1;  // the last region slot with off <= j holds member j
-        while (a < b) {
-          const int m = (a + b + 1) >> 1;
-          if (off[m] <= j) a = m; else b = m - 1;
-        }
-        const uint32_t key = rband[(size_t)(r0 + a) * rcap + abv[a] + (j - off[a])];
-        atomicAdd(&h[key & (kH3Bins - 1)], 1u);
-        const uint32_t slot = atomicAdd(&n2, 1u);
-        if (slot < (uint32_t)kC2Cap) {
-          c2key[slot] = key;
-          c2reg[slot] = (uint16_t)(r0 + a);
-        }
-      }
-      __syncthreads();
-    }
+    });
   }
   // class-2 members of the regions without stored band keys: from the lines
   // of those that hold any (their count is known from rsuf). Every workgroup reads
@@ -1363,7 +1327,8 @@ __global__ __launch_bounds__(NT, 4) void k_finish(
     for (uint32_t j = tid; j < n2; j += NT)
       if ((int)c2reg[j] < w) tally(c2key[j]);
   } else {
-    for_class2<NT>(w, B2, rcap, rcnt, rsuf, rband, off, abv, wsum, tally);
+    for_class2<NT>(tid < w ? c2at : 0u, c2above, rcap, rband, off, abv, wsum,
+                   [&](uint32_t key, int) { tally(key); });
   }
   lines_class2(w, [&](const uint32_t (&key)[4], uint32_t hits) {
 #pragma unroll
