@@ -21,6 +21,7 @@ import pytest
 import gen
 import oracle
 import paper_2010_10458_amd as tk
+import region_layout
 from gpu_common import announce, assert_bitwise, bits, need_gpu, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
@@ -196,13 +197,16 @@ def test_fp16_values_edge_magnitudes():
 
 def test_fp16_values_dense_regions():
     """A dense selection with binary16 values: 2^21 elements on a grid of
-    1/256 (ties), k = 150,000, so every selection region stores thousands of
-    candidates and the finish kernel writes them in rounds of one per
-    thread; globally and per tensor (two tensors)."""
+    1/256 (ties), k = 150,000, so every selection region stores more candidates
+    than its finish workgroup has threads, which writes them in rounds of one
+    per thread; globally and per tensor (two tensors)."""
     rng = np.random.default_rng(53)
     n = 1 << 21
     g = (np.round(rng.standard_normal(n) * 256) / 256).astype(np.float32)
     r = np.zeros(n, np.float32)
+    cand, _ = region_layout.counts(g, [n], 150_000)
+    a = region_layout.layout([n], 150_000)
+    assert cand.max() <= a["rcap"] and cand.min() > a["threads"]
     compare16([g], [r], k=150_000, label="dense fp16")
     h = n // 2
     compare16([g[:h], g[h:]], [r[:h], r[h:]], rho=0.07, mode=tk.PER_TENSOR,

@@ -13,6 +13,7 @@ import pytest
 import gen
 import oracle
 import paper_2010_10458_amd as tk
+import region_layout
 from gpu_common import (announce, assert_bitwise, bits, check_selection, need_gpu, to_dev,
                         to_host)
 
@@ -152,7 +153,8 @@ def test_per_tensor_many_groups():
 
 
 def test_unaligned_views():
-    """Tensors that start off a 16-byte boundary take the scalar path."""
+    """Tensors that start off a 16-byte boundary (read and written 16 bytes at a
+    time like the others; remainders element by element)."""
     import torch
     dev = need_gpu()
     rng = np.random.default_rng(400)
@@ -370,55 +372,63 @@ def test_ragged_list_between_one_and_two_units_per_workgroup(mode):
 
 @pytest.mark.parametrize("rho", [0.01, 0.05])
 def test_dense_selection_band_beyond_lds(rho):
-    """A dense selection on 10 M N(0, 1) elements: at rho = 0.05 a region of
-    the global selection holds about 8 K members of the threshold's level-1
-    bin, more than its workgroup keeps in LDS, so they are placed from a
-    second read of its lines."""
+    """A dense selection on 10 M N(0, 1) elements; at rho = 0.05 a quarter of them
+    lies in the threshold's level-1 bin, so that every region but the last holds
+    more band members than its workgroup keeps in LDS, though no more than it can
+    store: the rest goes through global scratch."""
     rng = np.random.default_rng(int(rho * 1000))
     n = 10_000_000
     g = rng.standard_normal(n).astype(np.float32)
     r = (rng.standard_normal(n) * 0.01).astype(np.float32)
+    if rho == 0.05:
+        pos = rng.choice(n, n // 4, replace=False)
+        g[pos] = (5 + 0.49 * rng.random(pos.size)) * rng.choice([-1, 1], pos.size)
+        r[pos] = 0.0
+        k = tk.k_from_rho(n, rho)
+        _, band = region_layout.counts(g + r, [n], k)
+        a = region_layout.layout([n], k)
+        assert band.max() <= a["rcap"] and (band[:-1] > region_layout.BAND_CAP).all()
     compare_with_oracle([g], [r], rho=rho, label=f"dense rho={rho}")
 
 
 @pytest.mark.parametrize("case", ["one_region", "two_regions_ties", "every_region"])
 def test_band_beyond_region_capacity(case):
-    """One exact selection over 2^20 elements (16 regions of 65,536 for the
-    selection kernels, each storing at most 4,608 candidates at k = 1,000 or
-    3,500) where one or two regions hold 6,000-10,000 members of the
-    threshold's level-1 bin: those regions store neither their candidates nor
-    their band, and every later step reads their lines instead. With ties:
-    the band takes its magnitudes from 700 values, so the threshold class is
-    split by position. Every region: all sixteen hold 6,000 band members."""
+    """One exact selection over 2^20 elements where one, two or all regions hold more
+    members of the threshold's level-1 bin than a region can store: those regions
+    store neither their candidates nor their band, and every later step reads
+    their lines instead. With ties: the band takes its magnitudes from 700
+    values, so the threshold class is split by position over both regions."""
     rng = np.random.default_rng({"one_region": 4242, "two_regions_ties": 4343}.get(case, 4444))
     n = 1 << 20
+    k = 3500 if case == "two_regions_ties" else 1000
+    a = region_layout.layout([n], k)
+    regions = {"one_region": [3], "two_regions_ties": [3, 9]}.get(case, range(a["count"]))
+    members = 10_000 if case == "one_region" else 6000
     g = (rng.standard_normal(n) * 0.1).astype(np.float32)
     top = rng.choice(n, 500, replace=False)
     g[top] = (10 + rng.random(500)).astype(np.float32) * rng.choice([-1, 1], 500)
-    if case == "one_region":
-        pos = 3 * 65536 + rng.choice(65536, 10_000, replace=False)
-        g[pos] = (5 + 0.5 * rng.random(pos.size)).astype(np.float32) * rng.choice([-1, 1], pos.size)
-        k = 1000
-    elif case == "every_region":
-        pos = np.concatenate([q * 65536 + rng.choice(65536, 6000, replace=False)
-                              for q in range(16)])
-        g[pos] = (5 + 0.5 * rng.random(pos.size)).astype(np.float32) * rng.choice([-1, 1], pos.size)
-        k = 1000
-    else:
-        vals = (5 + 0.5 * rng.random(700)).astype(np.float32)
-        pos = np.concatenate([3 * 65536 + rng.choice(65536, 6000, replace=False),
-                              9 * 65536 + rng.choice(65536, 6000, replace=False)])
+    pos = np.concatenate([q * a["elems"] + rng.choice(min(a["elems"], n - q * a["elems"]), members,
+                                                      replace=False) for q in regions])
+    if case == "two_regions_ties":
+        vals = (5 + 0.49 * rng.random(700)).astype(np.float32)
         g[pos] = rng.choice(vals, pos.size) * rng.choice([-1, 1], pos.size).astype(np.float32)
-        k = 3500
-    r = np.zeros(n, np.float32)
-    compare_with_oracle([g], [r], k=k, label=f"band beyond region capacity ({case})")
+    else:
+        g[pos] = (5 + 0.49 * rng.random(pos.size)).astype(np.float32) * rng.choice([-1, 1], pos.size)
+    _, band = region_layout.counts(g, [n], k)
+    assert list(np.flatnonzero(band > a["rcap"])) == list(regions)
+    _, val, _ = compare_with_oracle([g], [np.zeros(n, np.float32)], k=k,
+                                    label=f"band beyond region capacity ({case})")
+    if case == "two_regions_ties":  # (some of the threshold class is taken; it is in both)
+        T = np.abs(val).min()
+        eq = np.flatnonzero(np.abs(g) == T)
+        assert set(eq // a["elems"]) == {3, 9} and np.count_nonzero(np.abs(val) == T) < eq.size
 
 
 @pytest.mark.parametrize("levels", [3, 50])
 def test_dense_regions_with_ties_across_rounds(levels):
     """2^21 elements whose magnitudes take only `levels` values, k = 150,000:
-    each of the 32 selection regions stores several thousand candidates,
-    taken by the finish kernel in rounds of one candidate per thread, and the
+    each selection region stores several times as many candidates as its finish
+    workgroup has threads, taken in rounds of one candidate per thread, and the
     threshold class (tens of thousands of equal magnitudes, split by
     position) runs through many rounds of every region."""
     rng = np.random.default_rng(9100 + levels)
@@ -426,6 +436,9 @@ def test_dense_regions_with_ties_across_rounds(levels):
     mags = np.sort(rng.random(levels).astype(np.float32) + np.float32(0.5))
     g = (mags[rng.integers(0, levels, n)] * rng.choice([-1, 1], n)).astype(np.float32)
     r = np.zeros(n, np.float32)
+    cand, _ = region_layout.counts(g, [n], 150_000)
+    a = region_layout.layout([n], 150_000)
+    assert cand.max() <= a["rcap"] and cand.min() > 2 * a["threads"]
     idx, val, _ = compare_with_oracle([g], [r], k=150_000,
                                       label=f"dense ties across rounds ({levels} levels)")
     # the threshold class is split: some of its members are taken, some not
@@ -435,24 +448,27 @@ def test_dense_regions_with_ties_across_rounds(levels):
 
 
 def test_large_regions_with_ties_across_rounds():
-    """40 M elements, k = 200,000, values N(0, 1) rounded to multiples of
-    1/64: above 2^20 summary lines and with k < d / 160 the selection runs
-    1,024-thread workgroups (153 regions), each storing about 1,500
-    candidates, which the finish kernel takes in two rounds; the threshold
-    class (thousands of equal magnitudes) is split by position. Checked
-    through the exact selection properties against the oracle's x."""
+    """40 M elements, k = 1,000,000, values N(0, 1) rounded to multiples of
+    1/64: above 2^20 summary lines the selection runs 1,024-thread workgroups, each
+    of whose regions stores several thousand candidates, which the finish kernel
+    takes in rounds; the threshold class (thousands of equal magnitudes) is
+    split by position. Checked through the exact selection properties against
+    the oracle's x."""
     import torch
     dev = need_gpu()
     rng = np.random.default_rng(9200)
-    n = 40_000_000
+    n, k = 40_000_000, 1_000_000
     g = (np.round(rng.standard_normal(n) * 64) / 64).astype(np.float32)
-    announce("sparsify 40M quantized k=200000")
+    cand, _ = region_layout.counts(g, [n], k)
+    a = region_layout.layout([n], k)
+    assert a["threads"] == 1024 and cand.max() <= a["rcap"] and cand[:-1].min() > 3 * 1024
+    announce("sparsify 40M quantized k=1000000")
     gd, rd = torch.from_numpy(g).to(dev), torch.zeros(n, device=dev)
-    plan = tk.SparsifyPlan([n], k=200_000).bind([gd], [rd])
+    plan = tk.SparsifyPlan([n], k=k).bind([gd], [rd])
     idx, val = plan.execute()
     torch.cuda.synchronize()
     idx, val = idx.cpu().numpy(), val.cpu().numpy()
     x = orc().ef_add(g, np.zeros(n, np.float32))
-    check_selection(x, idx, val, rd.cpu().numpy(), 200_000)
+    check_selection(x, idx, val, rd.cpu().numpy(), k)
     T = np.abs(val).min()
     assert 0 < np.count_nonzero(np.abs(val) == T) < np.count_nonzero(np.abs(x) == T)

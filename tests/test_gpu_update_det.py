@@ -92,7 +92,7 @@ def test_det_overlap_bitwise(mode):
 
 def test_det_many_chunks_and_worker_batches():
     """P = 300 workers (two batches of 256), 2,000 entries each over three
-    tiles: tens of chunks of 1,024 entries per tile."""
+    tiles: hundreds of chunks of 768 entries per tile."""
     rng = np.random.default_rng(64)
     sizes = [8192 * 3]
     d = sizes[0]
@@ -116,8 +116,8 @@ def test_det_largest_worker_count():
 
 def test_det_repeats_hot_position_ragged_nnz_empty():
     """Repeats within a worker (one worker names position 7 fifty times),
-    forty workers all naming positions 7 and 8 (over a thousand entries of
-    one position in a chunk), zero and partial counts, empty lists."""
+    forty workers all naming positions 7 and 8 (over a thousand entries of each,
+    hundreds of them in one chunk), zero and partial counts, empty lists."""
     rng = np.random.default_rng(65)
     sizes = [20_000, 333]
     d = sum(sizes)
