@@ -218,24 +218,38 @@ def test_sparsify_region_splits(sizes, rho):
 
 
 # Segment search: lists that end just at, before and after the entries one
-# workgroup takes (512), empty lists among them, lists over few and many tiles.
-@pytest.mark.parametrize("k", [1, 255, 256, 257, 511, 512, 513, 1025])
-def test_update_list_lengths(k):
-    import torch
-    dev = need_gpu()
-    d, P = 300_007, 5
-    announce(f"update list lengths k={k}")
-    rng = np.random.default_rng(k)
-    idx = np.stack([np.sort(rng.choice(d, size=k, replace=False)) for _ in range(P)]).astype(np.int32)
+# workgroup takes: 256 with few entries in all (P = 5), 512 above 2^21 (P = 4,200);
+# empty lists and lists of one entry among them, lists over one and many tiles.
+def _list_lengths(d, P, k):
+    rng = np.random.default_rng([P, k])
+    if P == 5:
+        idx = np.stack([np.sort(rng.choice(d, size=k, replace=False)) for _ in range(P)])
+    else:  # (repeats within a list are allowed)
+        idx = np.sort(rng.integers(0, d, (P, k)), axis=1)
     idx[1] = np.sort(rng.choice(4096, size=k, replace=False))     # (one tile)
     val = rng.integers(-8, 9, (P, k)).astype(np.float32)          # (exact sums)
-    nnz = np.array([k, max(1, k - 1), 0, k // 2, k], np.int32)
+    nnz = np.tile([k, max(1, k - 1), 0, k // 2, k], P // 5).astype(np.int32)
+    if P > 5:
+        nnz[5::7] = 1
+        nnz[6::7] = np.minimum(k, 257)
+        assert P * k > 1 << 21
+    return idx.astype(np.int32), val, nnz
+
+
+@pytest.mark.parametrize("P,k", [(5, k) for k in (1, 255, 256, 257, 511, 512, 513, 1025)] +
+                         [(4200, k) for k in (511, 512, 513, 1025)])
+def test_update_list_lengths(P, k):
+    import torch
+    dev = need_gpu()
+    d = 300_007
+    announce(f"update list lengths P={P} k={k}")
+    idx, val, nnz = _list_lengths(d, P, k)
     w0 = np.zeros(d, np.float32)
     w = torch.zeros(d, device=dev)
     status = torch.zeros(1, dtype=torch.int32, device=dev)
     plan = tk.UpdatePlan([d], P=P, stride=k).bind([w])
-    plan.aggregate(torch.from_numpy(idx).to(dev), torch.from_numpy(val).to(dev),
-                   nnz=torch.from_numpy(nnz).to(dev), status=status)
+    it, vt = torch.from_numpy(idx).to(dev), torch.from_numpy(val).to(dev)
+    plan.aggregate(it, vt, nnz=torch.from_numpy(nnz).to(dev), status=status)
     torch.cuda.synchronize()
     assert int(status.item()) == 0
     for p in range(P):
@@ -243,10 +257,40 @@ def test_update_list_lengths(k):
     assert_bitwise(w.cpu().numpy(), w0, "sums")
     # the per-worker form, on the same lists
     w2 = torch.zeros(d, device=dev)
-    tk.aggregate_update([w2], [(torch.from_numpy(idx[p, :nnz[p]].copy()).to(dev),
-                                torch.from_numpy(val[p, :nnz[p]].copy()).to(dev))
-                               for p in range(P)], lr=-1.0)
+    tk.aggregate_update([w2], [(it[p, :nnz[p]], vt[p, :nnz[p]]) for p in range(P)], lr=-1.0)
     assert_bitwise(w2.cpu().numpy(), w0, "per-worker lists")
+
+
+# An entry past the end, a negative one and a pair out of order are reported by
+# either search, wherever in a workgroup's entries they lie (first, second half,
+# last entry of a list); the other tests show that good lists are not.
+@pytest.mark.parametrize("P,k", [(5, 513), (4200, 513)])
+@pytest.mark.parametrize("at", [0, 1, 255, 256, 257, 511, 512])
+def test_update_bad_entries_reported(P, k, at):
+    import torch
+    dev = need_gpu()
+    d = 300_007
+    idx, val, _ = _list_lengths(d, P, k)
+    vt = torch.from_numpy(val).to(dev)
+    w = torch.zeros(d, device=dev)
+    plan = tk.UpdatePlan([d], P=P, stride=k).bind([w])
+    for bad, bit in ((d, tk.STATUS_INDEX_RANGE), (-1, tk.STATUS_INDEX_RANGE),
+                     (None, tk.STATUS_UNSORTED)):
+        announce(f"bad entry {bad} at {at} P={P}")
+        x = idx.copy()
+        if bad is None:
+            j = max(at, 1)
+            x[P - 2, j - 1], x[P - 2, j] = 9, 8
+        else:
+            x[P - 2, at] = bad
+        it = torch.from_numpy(x).to(dev)
+        status = torch.zeros(1, dtype=torch.int32, device=dev)
+        plan.aggregate(it, vt, status=status)
+        torch.cuda.synchronize()
+        assert int(status.item()) & bit
+        with pytest.raises(tk.TkefStatusError) as ei:
+            tk.aggregate_update([w], [(it[p], vt[p]) for p in range(P)], lr=1.0)
+        assert ei.value.bits & bit
 
 
 # Entry search with few entries in a tile: worker counts around the powers of two
