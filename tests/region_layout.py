@@ -58,3 +58,29 @@ def counts(x, sizes, k):
     b1 = np.partition(top, x.size - k)[x.size - k]
     where, n = region_of(sizes, k), layout(sizes, k)["count"]
     return (np.bincount(where[top >= b1], minlength=n), np.bincount(where[top == b1], minlength=n))
+
+
+def sample_sizes(top):
+    """Sizes up to top: around the powers of two of tiles, spread ones between them,
+    each a whole number of tiles, one element more and a tile less one."""
+    rng = np.random.default_rng(3)
+    tiles = {top // TILE}
+    for e in range(int(np.log2(top // TILE)) + 1):
+        tiles |= {max(1, (1 << e) + s) for s in (-1, 0, 1)}
+        tiles |= {int(t) for t in rng.integers(1 << e, 2 << e, 6)}
+    return sorted({n for t in tiles for n in (t * TILE, t * TILE + 1, t * TILE + TILE - 1)
+                   if n <= top})
+
+
+def sample_ks(d, top):
+    """Values of k up to min(d, top): the ends, around the powers of two, and where
+    the lines per region meet one and four lines per thread or the even split."""
+    top = min(d, top)
+    a = layout([d], 1)
+    ks = {1, top}
+    for e in range(18):
+        ks |= {(1 << e) + s for s in (-1, 0, 1)}
+    for lines in (a["threads"], 2 * a["threads"], 4 * a["threads"], -(-a["nlines"] // 256)):
+        k = int(256.0 / 48.0 * d / lines)
+        ks |= {k + s for s in (-1, 0, 1)}
+    return sorted(k for k in ks if 1 <= k <= top)

@@ -8,6 +8,7 @@ import re
 import pytest
 
 import paper_2010_10458_amd as tk
+import region_layout
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "include", "tkef.h")
@@ -312,8 +313,11 @@ def test_aggregate_update_host_side():
 
 def test_static_entry_point_host_side():
     """tkef_sparsify1_static (no workspace): its limits are refused on the
-    host, and every single-tensor layout within them (each tile count up to
-    2^26 elements, with the largest k allowed) fits the fixed scratch."""
+    host, and the single-tensor layouts within them fit the fixed scratch: every
+    tile count up to 2^26 elements with the largest k allowed, and, since the
+    number of regions and their capacity also follow d / k, sampled sizes (full and
+    partial last tiles) with k from 1 to the largest, around its powers of two and
+    around the two ends of the region rule."""
     L = tk.lib()
     P_ = ctypes.c_void_p
     g, r, i, v = P_(0x1000), P_(0x40000000), P_(0x10), P_(0x20)
@@ -332,6 +336,11 @@ def test_static_entry_point_host_side():
         assert L.tkef_sparsify_workspace((ctypes.c_int64 * 1)(d), 1, tk.GLOBAL, 0.0, k,
                                          ctypes.byref(nb), None) == tk.OK
         worst = max(worst, nb.value)
+    for d in region_layout.sample_sizes(tk.STATIC_MAX_D):
+        for k in region_layout.sample_ks(d, tk.STATIC_MAX_K):
+            assert L.tkef_sparsify_workspace((ctypes.c_int64 * 1)(d), 1, tk.GLOBAL, 0.0, k,
+                                             ctypes.byref(nb), None) == tk.OK
+            worst = max(worst, nb.value)
     assert worst <= limit, worst
 
 
