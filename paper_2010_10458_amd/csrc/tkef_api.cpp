@@ -421,15 +421,18 @@ hipError_t run_one_group(const tkef_sparsify_plan_s* p, char* base, char* zb,
   return e;
 }
 
-// Persistent stream grid: four workgroups per compute unit, or three for large
-// inputs, above kStreamFewUnits units. With exactly three the three streams (g,
-// r, and r back) reach HBM at a higher rate: 340 M elements 745 -> 621 us (6.57
-// TB/s), 110 M 229 -> 214, 2^26 135 -> 130; 704, 736, 800, 832 or 896 workgroups
-// on 256 compute units are all slower than 768 (648-756 us at 340 M). Below
-// that size the rounds of units are too few for it to show (2^25: 67 -> 69 us)
-// and a fourth workgroup shortens the ends (3.2 M: 11.8 against 12.7 us). A
-// workgroup adds its histogram to the group's whenever the group changes, and
-// waits for that; where most units bring such a change (many tensors of a few
+// Persistent stream grid (of either selector's stream): four workgroups per compute
+// unit, or three for large inputs, above kStreamFewUnits units. With exactly three
+// the three streams (g, r, and r back) reach HBM at a higher rate: 340 M elements
+// 745 -> 621 us (6.57 TB/s), 110 M 219 -> 206, 2^26 131 -> 127.5; 704, 736, 800, 832
+// or 896 workgroups on 256 compute units are all slower than 768 (648-756 us at
+// 340 M). With gradients written just before: 340 M 751 -> 629, 110 M 227 -> 207, 2^26
+// 136 -> 128. MSTopK's stream: 340 M 725 -> 691, 110 M 220 -> 213, 2^26 134 -> 132, 56
+// M 114 -> 111. (A single call on an idle device does not reach that rate either
+// way: 2^26, the whole selection, 151 and 154.) Below that size the rounds of units
+// are too few for it to show (50.5 M 98.6 and 98.2, 2^25 67 and 69) and a fourth
+// workgroup shortens the ends (3.2 M: 11.8 against 12.7 us). A workgroup adds its
+// histogram to the group's whenever the group changes, and waits for that; where most units bring such a change (many tensors of a few
 // hundred units, each a group) the fourth workgroup covers the wait (60 M over
 // 300 tensors: 127 against 138 us), so three also need the changes, at most
 // min(units, workgroups) per group, to be no more than half of the units.

@@ -486,11 +486,13 @@ constexpr int kSWaves = kSBlock / 64;
 // workgroup, with more lines per thread, for inputs of up to kCSmallLines
 // summary lines: their per-thread steps (summaries, scans, bins) are short
 // instruction runs over every thread of a region, so fewer threads per
-// compute unit finish them sooner (25.6 M elements, collect and finish: 8.2 +
-// 6.9 against 9.4 + 8.6 us with kSBlock threads). Larger inputs take kSBlock
-// threads, whose regions hold more flagged lines (110 M, rho = 0.001: 18.6 +
-// 10.2 against 24.9 + 10.9 us; rho = 0.01: 69.7 + 30.0 against 74.2 + 31.0;
-// 340 M at 0.01: 265 + 114 against 251 + 119).
+// compute unit finish them sooner where few lines are flagged (25.6 M elements with
+// 1 % outliers, the selection: 67.9 us, with kSBlock threads 70.8; not where many
+// are: N(0, 1), 25.2 M, collect and finish 18.2 + 7.1 against 13.7 + 8.8). Larger
+// inputs take kSBlock threads, whose regions hold more flagged lines (N(0, 1), rho =
+// 0.001: 34 M 15.5 + 9.5 us, 19.8 + 7.2 with kCBlockSmall, 110 M 26.2 + 12.8 and 32.3
+// + 11.2; rho = 0.01: 110 M 76.6 + 32.3 and 86.4 + 32.1, 340 M 257 + 112 and 273 +
+// 116).
 constexpr int kCBlockSmall = 512;
 constexpr int64_t kCSmallLines = (int64_t)256 * kCBlockSmall * 8;
 constexpr int kSMaxGroups = 4096;
@@ -772,9 +774,13 @@ __device__ __forceinline__ void walk_cands(const TileDesc* __restrict__ tiles, i
 // times). A round lists its candidates in LDS, in position order; they are
 // then taken one per thread while the next round's lines are on their way.
 // (Before, each thread read a line and worked through its candidates, picked
-// from registers. collect, before and now, regions and rounds together: 256 K
-// elements 7.6 -> 6.7 us, 3.2 M 7.7 -> 6.7, 25.6 M 9.2 -> 8.2, 110 M 74 -> 70 at
-// rho = 0.01, 340 M 85 -> 67.)
+// from registers. collect, before and now, regions and rounds together. With
+// residuals that hold no mass just below the threshold: 256 K elements 7.6 -> 6.7
+// us, 3.2 M 7.7 -> 6.7, 25.6 M 9.2 -> 8.2, 110 M 74 -> 70 at rho = 0.01, 340 M 85 ->
+// 67. With residuals carried over 30 steps of fresh N(0, 1e-2) gradients, which
+// flag several times the lines: 256 K 15.2 -> 11.9, 3.2 M 16.2 -> 13.5, 25.6 M
+// 32.0 -> 29.0, 110 M 77.6 -> 66.2. Where most of the regions' flagged lines come to
+// just over a round, a second round shows: 25.6 M, N(0, 1), 17.5 -> 18.3.)
 // It writes
 //   rcand[w]    the candidates (key >= B1 << 20) in position order, as
 //               {global index, bits of x, address of the residual element};
@@ -1811,9 +1817,12 @@ typedef __attribute__((address_space(1))) const int32_t gint;
 // costs as much, and non-temporal or write-through stores 32 and 14 us). With
 // many entries a thread takes kSegPer = 2: P = 128 lists of 25,600 entries over
 // 6,240 tiles 10.2 -> 9.5 us; four 10.8, eight 11.1, two in 512-thread
-// workgroups 10.4. With few (up to kSegFew in all) it takes one: P = 40 lists
-// of 25,600 entries 5.0 us, 5.3 with two.
-constexpr int64_t kSegFew = (int64_t)1 << 21;
+// workgroups 10.4. With few, up to kSegFew in all, half as many wavefronts leave the
+// chip idle and it takes one. One and two entries per thread, lists over 3.2 /
+// 25.6 / 110 M positions: 0.5 M entries 4.6 / 4.8 / 4.8 and 4.6 / 5.0 / 4.9 us; 0.8
+// M 5.3 / 5.7 / 5.9 and 4.9 / 5.8 / 5.5; 1 M 5.6 / 6.0 / 6.6 and 5.2 / 5.8 / 6.1;
+// 2 M 8.2 / 9.2 / 10.3 and 7.2 / 8.9 / 9.8.
+constexpr int64_t kSegFew = (int64_t)1 << 19;
 template <bool kTable, int kSegPer>
 __global__ __launch_bounds__(256) void k_seg(ListsArg lists, int32_t P, int32_t d,
                                              int32_t ntiles_u, int32_t* __restrict__ seg,

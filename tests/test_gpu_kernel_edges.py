@@ -218,7 +218,7 @@ def test_sparsify_region_splits(sizes, rho):
 
 
 # Segment search: lists that end just at, before and after the entries one
-# workgroup takes: 256 with few entries in all (P = 5), 512 above 2^21 (P = 4,200);
+# workgroup takes: 256 with few entries in all (P = 5), 512 above 2^19 (P = 4,200);
 # empty lists and lists of one entry among them, lists over one and many tiles.
 def _list_lengths(d, P, k):
     rng = np.random.default_rng([P, k])
@@ -232,7 +232,7 @@ def _list_lengths(d, P, k):
     if P > 5:
         nnz[5::7] = 1
         nnz[6::7] = np.minimum(k, 257)
-        assert P * k > 1 << 21
+        assert P * k > 1 << 19
     return idx.astype(np.int32), val, nnz
 
 
